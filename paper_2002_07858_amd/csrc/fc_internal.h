@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "fc.h"
@@ -182,8 +183,11 @@ __host__ __device__ constexpr int split_rec_units(int N) { return code_rec_units
 // (N = 57: one) its products are cheaper on the vector ALUs than as nb tiles
 // that are mostly zero, so the record carries those L columns apart ("lead"
 // columns) and the tiles start at bin block k0 = 1; otherwise k0 = 0.  Tiles
-// (kb, r) with k0 <= kb <= r (rows 4r .. 4r+3, bins 4kb .. 4kb+3) run kb outer,
-// r inner.  Tile t's element A[i][k] = W'[4r + i][4kb + k] is stored at
+// (kb, r) with k0 <= kb <= r (rows 4r .. 4r+3, bins 4kb .. 4kb+3) run in
+// groups of at most kF64RowGroup row blocks: group outer, then kb, then r (the
+// scan finishes a group's rows before it starts the next one's, so it holds
+// one group's accumulators at a time; a row's bins still run in ascending
+// order).  Tile t's element A[i][k] = W'[4r + i][4kb + k] is stored at
 // position 4k + i of the tile; tiles are stored in pairs,
 // [pair][position][tile 2 pair + {0, 1}] doubles (an odd last pair padded
 // with zeros), so that one 16-byte LDS read at pair * 256 +
@@ -217,23 +221,39 @@ __host__ __device__ constexpr int f64_rec_doubles(int N)
     return f64_lead_double(N) + 4 * f64_nbe(N) * f64_lead(N);
 }
 __host__ __device__ constexpr int f64_rec_units(int N) { return f64_rec_doubles(N) / 2; }
-__host__ __device__ constexpr int f64_tile_kb(int N, int t)
+constexpr int kF64RowGroup = 4;
+__host__ __device__ constexpr int f64_ngroup(int N)
 {
-    int kb = f64_k0(N);
-    while (t >= f64_nb(N) - kb) {
-        t -= f64_nb(N) - kb;
-        ++kb;
-    }
-    return kb;
+    return (f64_nb(N) - f64_k0(N) + kF64RowGroup - 1) / kF64RowGroup;
 }
-__host__ __device__ constexpr int f64_tile_r(int N, int t)
+// First row block of group g; group ngroup starts past the last one.
+__host__ __device__ constexpr int f64_group_r0(int N, int g)
 {
-    int kb = f64_k0(N);
-    while (t >= f64_nb(N) - kb) {
-        t -= f64_nb(N) - kb;
-        ++kb;
+    return f64_ngroup(N) ? f64_k0(N) + (f64_nb(N) - f64_k0(N)) * g / f64_ngroup(N) : f64_nb(N);
+}
+struct F64Tile {
+    int g, kb, r;
+};
+__host__ __device__ constexpr F64Tile f64_tile_at(int N, int t)
+{
+    for (int g = 0; g < f64_ngroup(N); ++g) {
+        const int r0 = f64_group_r0(N, g), r1 = f64_group_r0(N, g + 1);
+        for (int kb = f64_k0(N); kb < r1; ++kb) {
+            const int first = kb > r0 ? kb : r0;  // rows max(kb, r0) .. r1-1
+            if (t < r1 - first) return F64Tile{g, kb, first + t};
+            t -= r1 - first;
+        }
     }
-    return kb + t;
+    return F64Tile{f64_ngroup(N), f64_nb(N), f64_nb(N)};
+}
+__host__ __device__ constexpr int f64_tile_kb(int N, int t) { return f64_tile_at(N, t).kb; }
+__host__ __device__ constexpr int f64_tile_r(int N, int t) { return f64_tile_at(N, t).r; }
+// First tile of group g (group ngroup: ntile).
+__host__ __device__ constexpr int f64_group_t0(int N, int g)
+{
+    int t = 0;
+    while (t < f64_ntile(N) && f64_tile_at(N, t).g < g) ++t;
+    return t;
 }
 
 // (minimum, first grid point reaching it) of one grid chunk of the FP64 scan.
@@ -242,11 +262,23 @@ struct Fp64Part {
     int64_t q;
 };
 
+#ifdef __HIPCC__
+// for (I = B; I < E; ++I) fn(integral_constant<I>), expanded at compile time
+// (loops over registers must be unrolled for their indices to be static; the
+// unroller gives up on the larger ones).
+template <int B, int E, class Fn>
+__device__ __forceinline__ void static_for(Fn &&fn)
+{
+    if constexpr (B < E) {
+        fn(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(fn);
+    }
+}
+
 // Copy one record of REC 16-byte units into LDS with direct global -> LDS
 // loads: thread tid moves units tid, tid + 256, ...; each wave's 64 lanes land
 // contiguously at its own base, so the LDS image equals the global record.  The loads are
 // waited for (vmcnt) before the barrier that hands the buffer over.
-#ifdef __HIPCC__
 template <int REC, int THREADS>
 __device__ __forceinline__ void record_to_lds(const uint4 *__restrict__ rec, uint4 *dst, int tid)
 {
@@ -261,6 +293,25 @@ __device__ __forceinline__ void record_to_lds(const uint4 *__restrict__ rec, uin
             __builtin_amdgcn_global_load_lds(
                 (const void *)(reinterpret_cast<const char *>(rec + c * THREADS) + lane_off),
                 (__attribute__((address_space(3))) void *)(dst + c * THREADS + wbase), 16, 0, 0);
+}
+
+// The same copy with buffer loads: the record's base goes in scalar registers
+// and the lane's offset is fixed, so a record costs no vector instruction (in
+// the FP64 scan those take time from the matrix cores: about 3 % there).  wbase
+// is the wave's first thread, wave-uniform.
+template <int REC, int THREADS>
+__device__ __forceinline__ void record_to_lds_sbase(const uint4 *rec, uint4 *dst, int tid, int wbase)
+{
+    constexpr int CPT = (REC + THREADS - 1) / THREADS;
+    // raw buffer over this record alone (0x00027000: 32-bit data format)
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(rec), 0, REC * 16,
+                                                        0x00027000);
+#pragma unroll
+    for (int c = 0; c < CPT; ++c)
+        if ((REC % THREADS) == 0 || c + 1 < CPT || c * THREADS + tid < REC)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rsrc, (__attribute__((address_space(3))) void *)(dst + c * THREADS + wbase), 16,
+                tid * 16, c * THREADS * 16, 0, 0);
 }
 
 __device__ __forceinline__ void wait_record_loads()

@@ -35,8 +35,6 @@
 #pragma once
 #include <stdint.h>
 
-#include <type_traits>
-
 #include "fc_internal.h"
 
 namespace fcx {
@@ -88,18 +86,6 @@ __device__ inline void split8(const float (&x)[8], uint4 &hi, uint4 &lo)
 // Materialise x here: without it the compiler may defer a register's updates
 // to its first use and keep every step's column values live until then.
 __device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
-
-// for (I = B; I < E; ++I) fn(integral_constant<I>), expanded at compile time
-// (the loops over a register row must be unrolled for its indices to be
-// static; the unroller gives up on the larger bin counts).
-template <int B, int E, class Fn>
-__device__ __forceinline__ void static_for(Fn &&fn)
-{
-    if constexpr (B < E) {
-        fn(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(fn);
-    }
-}
 
 // One step of either pass: a[k] = fma(-mul, c[k], a[k]) for J < k < NP, with
 // c = column J of the factorisation, read from `col` as 16-byte broadcasts in

@@ -1,0 +1,45 @@
+"""The scans at the edges of their tilings: bin counts at the borders of the
+kernels' row groups, universe counts at the borders of their tiles, grids of
+one, two and a few points, against the FP64 oracle (tolerances of the forms,
+as everywhere)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import parity
+from test_gpu_scan import FORM, fc, run_points, run_scan  # noqa: F401  (fc: fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def small_problem(N, G, K, seed):
+    """A smooth one-axis grid of G points and K universes at random true points."""
+    rng = np.random.default_rng([seed, N, G, K])
+    base = rng.uniform(80.0, 300.0, N)
+    S = base + np.linspace(0.0, 1.0, G)[:, None] * rng.uniform(0.0, 30.0, N)
+    A = rng.standard_normal((N, 2 * N))
+    F = 0.01 * (A @ A.T) / (2 * N)
+    F = 0.5 * (F + F.T)
+    p = np.sort(rng.integers(0, G, K))
+    d = S[p] + rng.standard_normal((K, N)) * np.sqrt(S[p])
+    return S, F, p, d
+
+
+def check(out, ref, S, F, d, p, tol):
+    assert np.all(np.abs(out["dchi2"] - ref["dchi2"]) <= tol * np.maximum(1.0, ref["chi2_p"]))
+    assert np.all(np.abs(out["chi2_p"] - ref["chi2_p"]) <= tol * np.maximum(1.0, ref["chi2_p"]))
+    clear = ref["chi2_2nd"] - ref["chi2_min"] > 2 * tol * np.maximum(1.0, ref["chi2_min"])
+    assert np.array_equal(out["argmin"][clear], ref["argmin"][clear])
+
+
+# bin blocks of four in row groups of four blocks, with no, one and two lead bins
+@pytest.mark.parametrize("N", [1, 2, 4, 5, 6, 16, 17, 18, 20, 21, 33, 36, 37, 49, 53, 58, 64])
+@pytest.mark.parametrize("K,G", [(1, 1), (31, 2), (33, 3), (127, 7), (129, 5)])
+def test_fp64_tiles_and_groups(fc, N, K, G):  # noqa: F811
+    S, F, p, d = small_problem(N, G, K, 1)
+    g = fc.fc_build_grid([np.arange(G, dtype=float)], S)
+    fc.fc_build_covariance(g, F, forms=FORM["fp64"])
+    ref = oracle.scan(S, F, d, p)
+    check(run_scan(fc, g, FORM["fp64"], d, p), ref, S, F, d, p, parity.TOL["fp64"])
