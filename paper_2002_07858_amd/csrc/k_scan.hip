@@ -24,6 +24,7 @@
 // Algorithm 1's rule that the lowest q wins exact ties whatever the split.
 #include "fc_internal.h"
 
+#include <algorithm>
 #include <utility>
 
 namespace fcx {
@@ -596,36 +597,38 @@ int resident_slots(const void *kernel, int block_threads)
     return cus * per_cu;
 }
 
-// Pick the number of grid chunks so that tiles x chunks fills the resident
-// block slots with the smallest tail: minimise ceil(tiles*c/slots)/c, with a
-// small charge per chunk.  With few tiles (a small K) every chunk count up to
-// G / min_chunk fits in one round and the most chunks win, so min_chunk sets
-// how far a small scan spreads over the CUs; at large K the tail term decides.
-ScanGeometry scan_geometry(int64_t K, int64_t G, int slots, int univ_per_block)
+// Grid chunks of a scan.  All blocks of a launch take about the same time, one
+// chunk each, so the launch takes rounds(c) = ceil(tiles c / slots) of them and
+// a half-empty last round is lost; c is the count that minimises
+//     rounds(c) (points per chunk + kChunkCost),
+// kChunkCost being a block's start (staging its universes) in points.  Chunks
+// are at most kChunkMax points long, so that the blocks that share a chunk stay
+// close and the L2 serves the later readers of each record, and at least
+// kChunkMin, which sets how far a small scan spreads over the CUs.  (FP64, 1000
+// tiles x 10 000 points on 768 slots: 5 chunks in 6.5 rounds 67.6 ms, 23 in
+// 29.95 rounds 65.2 ms; split FP16, 20 tiles x 216 000 points on 512 slots: 106
+// chunks in 4.1 rounds 12.7 ms, 128 in 5.0 rounds 11.0 ms.)
+ScanGeometry scan_geometry(int64_t n_utiles, int64_t tiles, int64_t G, int slots,
+                           int64_t max_chunks)
 {
+    constexpr int64_t kChunkMax = 2048, kChunkMin = 4, kChunkCost = 2;
     ScanGeometry sg;
-    sg.n_utiles = (K + univ_per_block - 1) / univ_per_block;
-    const int64_t min_chunk = 8;
-    int64_t cmax = G / min_chunk;
-    if (cmax < 1) cmax = 1;
-    if (cmax > 256) cmax = 256;
-    // keep blocks * 256 work-items well inside the 32-bit dispatch size
-    const int64_t max_blocks = int64_t(1) << 23;
-    const int64_t cfit = max_blocks / (sg.n_utiles > 0 ? sg.n_utiles : 1);
-    if (cmax > cfit) cmax = cfit > 0 ? cfit : 1;
-    double best = 1e300;
-    int64_t bestc = 1;
-    for (int64_t c = 1; c <= cmax; ++c) {
-        const int64_t units = sg.n_utiles * c;
-        const double rounds = (double)((units + slots - 1) / slots);
-        const double cost = rounds / (double)c * (1.0 + 0.002 * (double)c);  // chunk overhead
-        if (cost < best * (1.0 - 1e-9)) {
+    sg.n_utiles = n_utiles;
+    // blocks x 256 work-items stay well inside the 32-bit dispatch size
+    const int64_t fit = (int64_t(1) << 23) / std::max<int64_t>(n_utiles, 1);
+    const int64_t cap = std::max<int64_t>(1, std::min(max_chunks, fit));
+    const int64_t lo = std::min(cap, (G + kChunkMax - 1) / kChunkMax);
+    const int64_t hi = std::min(cap, std::max(lo, std::min(G / kChunkMin, 2 * lo + 512)));
+    int64_t best = INT64_MAX;
+    for (int64_t c = lo; c <= hi; ++c) {
+        const int64_t q = (G + c - 1) / c, n = (G + q - 1) / q;
+        const int64_t cost = (tiles * n + slots - 1) / slots * (q + kChunkCost);
+        if (cost < best) {
             best = cost;
-            bestc = c;
+            sg.q_per_chunk = q;
+            sg.n_qchunks = n;
         }
     }
-    sg.q_per_chunk = (G + bestc - 1) / bestc;
-    sg.n_qchunks = (G + sg.q_per_chunk - 1) / sg.q_per_chunk;
     return sg;
 }
 
@@ -637,20 +640,8 @@ static hipError_t launch_fp32_n(const fc_grid *g, int64_t K, const double *d, co
     // resident block slots: queried once per instantiation (thread-safe)
     static const int slots =
         resident_slots(reinterpret_cast<const void *>(&k_scan_fp32<N>), 64 * kWavesPerBlock);
-    ScanGeometry sg = scan_geometry(K, nq, slots, kFp32UnivPerBlock);
-    // then chunks of at most kFp32ChunkMax points, as far as the dispatch size
-    // allows, as in the points form (c3: 1.59 s against 1.68 s, c5 0.5 %
-    // faster; the same results bit for bit)
-    constexpr int64_t kFp32ChunkMax = 2048;
-    if (sg.q_per_chunk > kFp32ChunkMax) {
-        const int64_t cap = (int64_t(1) << 23) / (sg.n_utiles > 0 ? sg.n_utiles : 1);
-        int64_t nc = (nq + kFp32ChunkMax - 1) / kFp32ChunkMax;
-        if (nc > cap) nc = cap;
-        if (nc > sg.n_qchunks) {
-            sg.q_per_chunk = (nq + nc - 1) / nc;
-            sg.n_qchunks = (nq + sg.q_per_chunk - 1) / sg.q_per_chunk;
-        }
-    }
+    const int64_t tiles = (K + kFp32UnivPerBlock - 1) / kFp32UnivPerBlock;
+    const ScanGeometry sg = scan_geometry(tiles, tiles, nq, slots, nq);
     const int64_t blocks = sg.n_utiles * sg.n_qchunks;
     ProfScope prof(st, "k_scan_fp32");
     hipLaunchKernelGGL((k_scan_fp32<N>), dim3((unsigned)blocks), dim3(64 * kWavesPerBlock), 0, st,
@@ -702,21 +693,11 @@ static hipError_t launch_fp32_pts_n(const fc_grid *g, int64_t n_pts, const int64
     const int64_t max_tiles = K / kPtsTile + n_pts;  // bound on the dense tile count
     const int64_t groups_per_xcd = (max_tiles + 63) / 64;
     const int64_t n_tiles = 64 * groups_per_xcd;    // blocks per grid chunk
-    ScanGeometry sg = scan_geometry(max_tiles * kPtsTile, nq, slots, kPtsTile);
-    // then shorter chunks, of at most kPtsChunkMax points, as far as the
-    // dispatch size allows: the tiles that share a chunk start together and
-    // stay close, so the L2 serves the later readers of each record (c5:
-    // 4.65 s against 4.81 s for the whole call, the same results bit for bit)
-    constexpr int64_t kPtsChunkMax = 2048;
-    if (sg.q_per_chunk > kPtsChunkMax) {
-        const int64_t cap = (int64_t(1) << 23) / n_tiles;
-        int64_t nc = (nq + kPtsChunkMax - 1) / kPtsChunkMax;
-        if (nc > cap) nc = cap;
-        if (nc > sg.n_qchunks) {
-            sg.q_per_chunk = (nq + nc - 1) / nc;
-            sg.n_qchunks = (nq + sg.q_per_chunk - 1) / sg.q_per_chunk;
-        }
-    }
+    // tiles with work if the segments are about equally long (their lengths are
+    // known on the device only)
+    const int64_t len = (K + n_pts - 1) / n_pts;
+    const int64_t tiles = std::min(max_tiles, n_pts * ((len + kPtsTile - 1) / kPtsTile));
+    const ScanGeometry sg = scan_geometry(n_tiles, tiles, nq, slots, nq);
     const int64_t blocks = n_tiles * sg.n_qchunks;
     hipLaunchKernelGGL(k_tile_prefix, dim3(1), dim3(1024), 0, st, n_pts, seg_off, tile_start);
     ProfScope prof(st, "k_scan_fp32_pts");

@@ -48,7 +48,6 @@ namespace {
 constexpr int kF64Waves = 4;                       // waves per block
 constexpr int kF64Sets = 2;                        // sets of 16 universes per wave
 constexpr int kF64Univ = 16 * kF64Sets * kF64Waves;  // universes per block (128)
-constexpr int64_t kF64ChunkMax = 2048;                // grid points per block at most
 constexpr size_t kF64PartsMax = size_t(2) << 30;      // bytes of chunk partials at most
 
 constexpr int kF64Ahead = 2;  // tile pairs read from LDS ahead of their MFMAs
@@ -330,23 +329,10 @@ hipError_t launch_f64m_n(const fc_grid *g, int64_t K, const double *d, const int
     static const int slots =
         resident_slots(reinterpret_cast<const void *>(&k_scan_f64m<N>), 64 * kF64Waves);
     const int64_t G = g->G;
-    // chunks: the fewest that fill the resident slots with a small tail
-    ScanGeometry sg = scan_geometry(K, G, slots, kF64Univ);
+    const int64_t tiles = (K + kF64Univ - 1) / kF64Univ;
+    const ScanGeometry sg = scan_geometry(
+        tiles, tiles, G, slots, (int64_t)(kF64PartsMax / (sizeof(Fp64Part) * (size_t)K)));
     int64_t chunks = sg.n_qchunks, qpc = sg.q_per_chunk;
-    // then shorter chunks, of at most kF64ChunkMax points, as far as the
-    // dispatch size and the partials' bound allow (c5: 9.11 s against 9.27 s
-    // with the 11 chunks of 95 326 points above; same results bit for bit)
-    if (qpc > kF64ChunkMax) {
-        const int64_t by_dispatch = (int64_t(1) << 23) / (sg.n_utiles > 0 ? sg.n_utiles : 1);
-        const int64_t by_parts = (int64_t)(kF64PartsMax / (sizeof(Fp64Part) * (size_t)K));
-        int64_t nc = (G + kF64ChunkMax - 1) / kF64ChunkMax;
-        if (nc > by_dispatch) nc = by_dispatch;
-        if (nc > by_parts) nc = by_parts;
-        if (nc > chunks) {
-            qpc = (G + nc - 1) / nc;
-            chunks = (G + qpc - 1) / qpc;
-        }
-    }
     // the partials must fit the scratch (library-owned or the caller's)
     const int64_t max_chunks = (int64_t)(scratch_bytes / (sizeof(Fp64Part) * (size_t)K));
     Fp64Part *part = nullptr;

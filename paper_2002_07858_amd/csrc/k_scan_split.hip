@@ -424,13 +424,6 @@ static int resident_slots_split(const void *kernel)
 }
 
 constexpr int kSplitColBlocks = 4;  // 64 universes per wave
-// Grid points per block at most.  The blocks that share a chunk read the
-// same records in the same order, and the L2 serves the later readers only
-// while the blocks stay within a few hundred points of each other; short
-// chunks restart them together often (c5, 2048 instead of 25 600 points:
-// split FP16 7.6 -> 5.6 TB fetched, 1.82 -> 1.66 s; BF16 3.3 -> 1.2 TB).
-constexpr int64_t kSplitChunkMax = 2048;
-
 // Every layout split_code gives for N = 1..64 (step counts of the row groups).
 #define FC_SPLIT_CODES(X)                                                                   \
     X(0x0001) X(0x0002) X(0x0021) X(0x0031) X(0x0032) X(0x0421) X(0x0431) X(0x0532)        \
@@ -458,18 +451,9 @@ static hipError_t launch_split_t(const fc_grid *g, int64_t K, const double *d,
     // resident block slots: queried once per instantiation (thread-safe)
     static const int slots =
         resident_slots_split(reinterpret_cast<const void *>(&k_scan_split<CODE, NC, FP16>));
-    ScanGeometry sg = scan_geometry(K, nq, slots, 16 * NC * kWavesPerBlock);
-    if (sg.q_per_chunk > kSplitChunkMax) {
-        // shorter chunks, as many as keep blocks x 256 work-items within the
-        // 32-bit dispatch size (the general geometry's bound)
-        const int64_t cap = (int64_t(1) << 23) / (sg.n_utiles > 0 ? sg.n_utiles : 1);
-        int64_t nc = (nq + kSplitChunkMax - 1) / kSplitChunkMax;
-        if (nc > cap) nc = cap;
-        if (nc > sg.n_qchunks) {
-            sg.q_per_chunk = (nq + nc - 1) / nc;
-            sg.n_qchunks = (nq + sg.q_per_chunk - 1) / sg.q_per_chunk;
-        }
-    }
+    constexpr int64_t tile = 16 * NC * kWavesPerBlock;
+    const int64_t tiles = (K + tile - 1) / tile;
+    const ScanGeometry sg = scan_geometry(tiles, tiles, nq, slots, nq);
     const int64_t blocks = sg.n_utiles * sg.n_qchunks;
     const uint4 *R = FP16 ? g->RH16 : g->RB16;
     ProfScope prof(st, "k_scan_split");
