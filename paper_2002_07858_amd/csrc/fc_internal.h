@@ -25,8 +25,11 @@
 // row block is the narrowest one.  Row block b (padded rows 4b .. 4b+3) needs
 // padded bins k' <= 4b + 3.  The (k', b) pairs are enumerated k' outer
 // (0 .. 4ns-1), b inner (k'/4 .. ns-1): npair = 2 ns (ns+1); the P ns pairs
-// with k' < P are zero and skipped by the scan (N = 57: 435 of 480).  Pair t
-// lives in A register t/16, slot t%16; lane 4 (t%16) + m holds
+// with k' < P are zero and skipped by the scan (N = 57: 435 of 480).  In the
+// record the pairs run in groups of at most kFp32RowGroup row blocks (group
+// outer, then k', then b): the scan finishes a group's rows before it starts
+// the next one's.  The pair at position i lives in A register i/16, slot i%16;
+// lane 4 (i%16) + m holds
 //     W_q[4b + m - P][k' - P]                    (zero outside the triangle)
 // Per grid point the A registers are stored lane-major in groups of four,
 //     A[v/4][lane][v%4]               (ng = ceil(npair/64) groups of 1 KB)
@@ -79,6 +82,34 @@ __host__ __device__ constexpr int fp32_pair_b(int ns, int t)
 {
     const int kp = fp32_pair_kp(ns, t);
     return kp / 4 + (t - fp32_pair_index(ns, kp, kp / 4));
+}
+
+constexpr int kFp32RowGroup = 5;
+__host__ __device__ constexpr int fp32_ngroup(int ns) { return ceil_div(ns, kFp32RowGroup); }
+// First row block of group g; group ngroup starts past the last one.
+__host__ __device__ constexpr int fp32_group_b0(int ns, int g) { return ns * g / fp32_ngroup(ns); }
+// First position of group g.
+__host__ __device__ constexpr int fp32_group_i0(int ns, int g)
+{
+    int i = 0;
+    for (int h = 0; h < g; ++h) {
+        const int b0 = fp32_group_b0(ns, h), b1 = fp32_group_b0(ns, h + 1);
+        for (int kp = 0; kp < 4 * b1; ++kp) i += b1 - (kp / 4 > b0 ? kp / 4 : b0);
+    }
+    return i;
+}
+// The pair at position i of the record.
+__host__ __device__ constexpr int fp32_pair_at(int ns, int i)
+{
+    for (int g = 0; g < fp32_ngroup(ns); ++g) {
+        const int b0 = fp32_group_b0(ns, g), b1 = fp32_group_b0(ns, g + 1);
+        for (int kp = 0; kp < 4 * b1; ++kp) {
+            const int first = kp / 4 > b0 ? kp / 4 : b0;
+            if (i < b1 - first) return fp32_pair_index(ns, kp, first + i);
+            i -= b1 - first;
+        }
+    }
+    return fp32_npairs(ns);
 }
 
 // ---------------------------------------------------------------------------
@@ -365,14 +396,15 @@ inline void cov_map_fp64(int N, int16_t *m)
 }
 
 // FP32 record, its W_q part: one entry per float (4 rec_w_units(ns) entries),
-// A[v/4][lane][v%4] with lane 4 X + m holding pair t = 16 v + X.
+// A[v/4][lane][v%4] with lane 4 X + m holding the pair at position 16 v + X.
 inline void cov_map_fp32(int ns, int N, int16_t *m)
 {
     const int P = fp32_pad(ns, N), np = fp32_npairs(ns);
     for (int v = 0; v < 4 * n_groups_from_ns(ns); ++v)
         for (int lane = 0; lane < 64; ++lane) {
-            const int t = 16 * v + (lane >> 2), mm = lane & 3;
+            const int i = 16 * v + (lane >> 2), mm = lane & 3;
             int16_t x = kMapZero;
+            const int t = fp32_pair_at(ns, i);
             if (t < np)
                 x = map_w(N, 4 * fp32_pair_b(ns, t) + mm - P, fp32_pair_kp(ns, t) - P);
             m[((v >> 2) * 64 + lane) * 4 + (v & 3)] = x;

@@ -9,9 +9,19 @@
 // lane blocks.  The 4-row granularity covers the lower triangle with little
 // waste (N = 57: 1740 issued multiply-adds per evaluation for 1653 needed),
 // and each lane ends with its own universe's rows, so chi2 is a lane-local
-// sum of squares followed by a strict-"<" running minimum.  Vector
-// instructions do not overlap the FP32 MFMAs on this chip, so the vector work
-// around them (residuals, squares) is kept to few FP32 instructions.
+// sum of squares followed by a strict-"<" running minimum.  On this chip a
+// vector instruction takes 4 cycles of a SIMD that the FP32 MFMAs (8 cycles
+// each) cannot use and every change from MFMAs to vector work and back 8 more,
+// and one wave alone issues an MFMA every 11.5 cycles, two every 8.5, three
+// every 8.3.  The rows are therefore contracted in groups of kFp32RowGroup row
+// blocks: one vector phase per group, and one group's accumulators live
+// instead of all, which leaves the offset form below 128 registers (four waves
+// per SIMD, two before) and the residual form's residuals formed once per
+// point at two waves per SIMD.  The launch is then bound by power: the matrix
+// cores are 92 % busy at 2.22 GHz (85 % at 2.31 GHz before; offset form, 100 x
+// 100 points, N = 57, 256 x 2000 universes: 142.1 -> 137.3 ms; residual form,
+// 27 000 points x 20 000 universes: 17.4 -> 16.9 ms; three waves per SIMD with
+// the universes' low parts in LDS 16.9-17.1 ms).
 //
 // Work decomposition: a 256-thread block owns 256 universes (one per lane)
 // and walks a contiguous range of grid points in list order.  Each lane
@@ -36,21 +46,8 @@ __device__ __forceinline__ float pick(const float4 &v, int c)
     return c == 0 ? v.x : (c == 1 ? v.y : (c == 2 ? v.z : v.w));
 }
 
-// Sixteen signal values, read through the scalar cache (uniform per wave).
-struct Sig16 {
-    float v[16];
-};
-typedef const __attribute__((address_space(4))) Sig16 *sig_ptr;
-__device__ __forceinline__ Sig16 load_sig(sig_ptr p, int i)
-{
-    Sig16 r;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) r.v[k] = p[i].v[k];
-    return r;
-}
-
-// Per-universe state a lane carries through its range of grid points.  The
-// universe is held as d = dh + dl: dh = float(d) and dl, the rest, as FP16
+// A universe as its lane carries it through its range of grid points.  It
+// is held as d = dh + dl: dh = float(d) and dl, the rest, as FP16
 // scaled by a per-universe power of two 2^e (so that the largest |dl| 2^e
 // lies in [2^14, 2^15)); dl 2^e keeps 11 bits, so d is carried to 35 bits,
 // and the residual costs one subtraction and one mixed FP16/FP32 FMA.
@@ -59,12 +56,6 @@ struct Fp32Lane {
     float dh[N];
     uint32_t dl[(N + 1) / 2];  // dl 2^e as FP16, bins 2i (low half) and 2i+1 (high half)
     float dl_scale;            // 2^-e
-    Sig16 s0;                  // the next grid point's first 16 signal values
-    int64_t p_own;       // the universe's true point (-1: no universe)
-    float best;          // running minimum and its grid point
-    uint32_t qbest;
-    float cp;            // chi2 at the true point, once seen
-    bool have_cp;
 };
 
 // r = dl 2^-e + t with dl taken from one FP16 half of a packed register: the
@@ -78,173 +69,110 @@ __device__ __forceinline__ float fma_mix_dl(uint32_t dl2, float scale, float t)
     return __builtin_fmaf((float)h[HI], scale, t);
 }
 
-// Per-grid-point operands: the A-register group being consumed and the next
-// one (prefetched from LDS), the current and next 16 signal values (scalar
-// registers) and the residual of the current bin.
-constexpr int kResGroup = 8;  // residuals formed together (bins)
-
-struct Fp32Ops {
-    float4 a_cur, a_nxt;
-    Sig16 s_cur, s_nxt;
-    float r[kResGroup];  // residuals of the current group of bins
-};
-
-// Residual of real bin K into o.r[K % kResGroup], rotating the signal chunks
-// when K starts a new one; with the last chunk in use, the next grid point's
-// first chunk is fetched.
-template <int N, int K>
-__device__ __forceinline__ void fp32_residual(Fp32Ops &o, Fp32Lane<N> &L, sig_ptr sg,
-                                              sig_ptr sg_next, bool more)
+// Sums of squares over row blocks B0 .. B1-1 into the lane's four FP32 chains
+// (one per row of a block; the P padding rows of block 0 are zero and skipped).
+template <int P, int B0, int B1, int NS>
+__device__ __forceinline__ void fp32_squares(const v4f (&acc)[NS], float (&part)[4])
 {
-    constexpr int NCH = (N + 15) / 16;  // 16-value signal chunks
-    if constexpr (K < N) {
-        if constexpr (K % 16 == 0) {
-            if constexpr (K > 0) o.s_cur = o.s_nxt;
-            if constexpr (K / 16 + 1 < NCH) o.s_nxt = load_sig(sg, K / 16 + 1);
-            if constexpr (K / 16 + 1 == NCH)
-                if (more) L.s0 = load_sig(sg_next, 0);
-        }
-        const float t = L.dh[K] - o.s_cur.v[K % 16];
-        o.r[K % kResGroup] = fma_mix_dl<K & 1>(L.dl[K / 2], L.dl_scale, t);
-    }
-}
-
-// Pair T of the enumeration: rotate the A groups at a group boundary, form
-// the residuals of a group of kResGroup bins at the first pair of the
-// group's first bin, and issue one 4x4x1 MFMA whose A slice is broadcast
-// from slot T % 16 of register T / 16.  Vector instructions do not overlap
-// the FP32 MFMAs, and each switch from MFMAs to vector work costs about one
-// MFMA's latency, so the residuals are formed in groups rather than one per
-// bin.  Padded bins left of the shift (k' < P) are zero and generate no code.
-template <int N, int T>
-__device__ __forceinline__ void fp32_pair(v4f (&acc)[n_ksteps(N)], Fp32Ops &o, Fp32Lane<N> &L,
-                                          const float4 *__restrict__ wl, sig_ptr sg,
-                                          sig_ptr sg_next, bool more, int lane)
-{
-    constexpr int NS = n_ksteps(N), P = fp32_pad(NS, N);
-    constexpr int KP = fp32_pair_kp(NS, T), B = fp32_pair_b(NS, T);
-    constexpr int V = T / 16, NG = n_groups_from_ns(NS);
-    if constexpr (T % 64 == 0 && T > 0) {
-        o.a_cur = o.a_nxt;
-        if constexpr (T / 64 + 1 < NG) o.a_nxt = wl[(T / 64 + 1) * 64 + lane];
-    }
-    if constexpr (KP >= P) {
-        constexpr int K = KP - P;
-        if constexpr (B == KP / 4 && K % kResGroup == 0) {
-            static_assert(kResGroup == 8, "eight residuals per group");
-            fp32_residual<N, K>(o, L, sg, sg_next, more);
-            fp32_residual<N, K + 1>(o, L, sg, sg_next, more);
-            fp32_residual<N, K + 2>(o, L, sg, sg_next, more);
-            fp32_residual<N, K + 3>(o, L, sg, sg_next, more);
-            fp32_residual<N, K + 4>(o, L, sg, sg_next, more);
-            fp32_residual<N, K + 5>(o, L, sg, sg_next, more);
-            fp32_residual<N, K + 6>(o, L, sg, sg_next, more);
-            fp32_residual<N, K + 7>(o, L, sg, sg_next, more);
-            // keep the group's vector work together, ahead of its MFMAs
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        acc[B] = __builtin_amdgcn_mfma_f32_4x4x1f32(pick(o.a_cur, V % 4), o.r[K % kResGroup],
-                                                    acc[B], 4, T % 16, 0);
-        // one group of bins at a time: keeps the scheduler from hoisting
-        // operands of later bins (register pressure)
-        if constexpr (B == NS - 1 && K % kResGroup == kResGroup - 1)
-            __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-template <int N, int... Ts>
-__device__ __forceinline__ void fp32_pairs(v4f (&acc)[n_ksteps(N)], Fp32Ops &o, Fp32Lane<N> &L,
-                                           const float4 *__restrict__ wl, sig_ptr sg,
-                                           sig_ptr sg_next, bool more, int lane,
-                                           std::integer_sequence<int, Ts...>)
-{
-    (fp32_pair<N, Ts>(acc, o, L, wl, sg, sg_next, more, lane), ...);
-}
-
-// chi2 = the lane's sum of squares (four FP32 chains over the row blocks; the
-// P padding rows of block 0 are zero and skipped), folded into the running
-// minimum with Algorithm 1's strict "<", and kept when q is the true point.
-template <int NS, int P>
-__device__ __forceinline__ void fp32_fold(const v4f (&acc)[NS], int64_t q, int64_t p_own,
-                                          float &best, uint32_t &qbest, float &cp, bool &have_cp)
-{
-    float part[4];
+    static_for<B0, B1>([&](auto bc) {
+        constexpr int b = decltype(bc)::value;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        part[j] = (j >= P) ? acc[0][j] * acc[0][j] : 0.0f;
-#pragma unroll
-        for (int b = 1; b < NS; ++b) part[j] = fmaf(acc[b][j], acc[b][j], part[j]);
-    }
-    const float chi2 = (part[0] + part[1]) + (part[2] + part[3]);
-    if (q == p_own) {
-        cp = chi2;
-        have_cp = true;
-    }
-    if (chi2 < best) {
-        best = chi2;
-        qbest = (uint32_t)q;
-    }
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (b == 0)
+                part[j] = (j >= P) ? acc[0][j] * acc[0][j] : 0.0f;
+            else
+                part[j] = fmaf(acc[b][j], acc[b][j], part[j]);
+        }
+    });
 }
 
-// One grid point: contract the record in `cur`, fold chi2 into the running
-// minimum, and (if more) bring the next record into `nxt`.  The two LDS
-// buffers are separate objects so that the compiler can tell the copy into
-// one from the reads of the other.  The signal values come from the record in
-// global memory through scalar loads (read-only data, uniform addresses).
+// The squares of z = W_q r + c0 of one grid point, group by group: part's four
+// chains add up to chi2.  wl: the record's A slices at this lane, c0: the rows'
+// starts (the same in every lane), both in LDS; r: the lane's universe at
+// every bin.  Padded bins left of the shift (k' < P) are zero and generate no
+// code.
 template <int N>
-__device__ __forceinline__ void fp32_point(int64_t q, bool more, const uint4 *__restrict__ R32,
-                                           const uint4 *cur, uint4 *nxt, Fp32Lane<N> &L)
+__device__ __forceinline__ void fp32_contract(const float4 *wl, const float4 *c0,
+                                              const float (&r)[N], float (&part)[4])
 {
-    constexpr int NS = n_ksteps(N), P = fp32_pad(NS, N);
-    constexpr int NWU = rec_w_units(NS);
-    constexpr int REC = rec_units(NS);
-    constexpr int THREADS = 64 * kWavesPerBlock;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-
-    // signal values through the scalar cache (the first 16 were fetched during
-    // the previous grid point); then the next record's copy, before the
-    // contraction
-    // the packed FP16 parts are re-presented to the compiler at every grid
-    // point, so that their FP32 conversions stay inside the mixed FMAs
-    // instead of being hoisted out of the grid loop into extra registers
-#pragma unroll
-    for (int i = 0; i < (N + 1) / 2; ++i) asm volatile("" : "+v"(L.dl[i]));
-    Fp32Ops o;
-    sig_ptr sg = (sig_ptr)(R32 + q * REC + NWU);  // Sh, real bins
-    sig_ptr sg_next = (sig_ptr)(R32 + (q + 1) * REC + NWU);
-    o.s_cur = L.s0;
-    if (more) record_to_lds<REC, THREADS>(R32 + (q + 1) * REC, nxt, tid);
-    __builtin_amdgcn_sched_barrier(0);
-
-    const float4 *wl = reinterpret_cast<const float4 *>(cur);
-    const float4 *cl = reinterpret_cast<const float4 *>(cur + NWU) + 16;  // C, 16 x float4
-    // accumulators start at C_q (the same four rows in every lane)
+    constexpr int NS = n_ksteps(N), P = fp32_pad(NS, N), NG = fp32_ngroup(NS);
+    constexpr int NA = n_groups_from_ns(NS);
+    float4 a[NA];  // four A registers each, read 32 pairs ahead
     v4f acc[NS];
-#pragma unroll
-    for (int b = 0; b < NS; ++b) {
-        const float4 cv = cl[b];
-        acc[b] = v4f{cv.x, cv.y, cv.z, cv.w};
-    }
-    o.a_cur = wl[lane];
-    if constexpr (n_groups_from_ns(NS) > 1) o.a_nxt = wl[64 + lane];
-    fp32_pairs<N>(acc, o, L, wl, sg, sg_next, more, lane,
-                  std::make_integer_sequence<int, fp32_npairs(NS)>{});
-
-    fp32_fold<NS, P>(acc, q, L.p_own, L.best, L.qbest, L.cp, L.have_cp);
-
-    if (more) wait_record_loads();
-    __syncthreads();
+    a[0] = wl[0];
+    static_for<0, NG>([&](auto gc) {
+        constexpr int g = decltype(gc)::value;
+        constexpr int B0 = fp32_group_b0(NS, g), B1 = fp32_group_b0(NS, g + 1);
+        static_for<B0, B1>([&](auto bc) {
+            constexpr int b = decltype(bc)::value;
+            const float4 cv = c0[b];
+            acc[b] = v4f{cv.x, cv.y, cv.z, cv.w};
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (g > 0) {  // while the starts arrive
+            fp32_squares<P, fp32_group_b0(NS, g - 1), B0>(acc, part);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        static_for<fp32_group_i0(NS, g), fp32_group_i0(NS, g + 1)>([&](auto ic) {
+            constexpr int i = decltype(ic)::value, t = fp32_pair_at(NS, i), v = i / 16;
+            constexpr int kp = fp32_pair_kp(NS, t), b = fp32_pair_b(NS, t);
+            if constexpr (i % 64 == 32 && i / 64 + 1 < NA) a[i / 64 + 1] = wl[(i / 64 + 1) * 64];
+            if constexpr (kp >= P)
+                acc[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(pick(a[i / 64], v % 4), r[kp - P],
+                                                            acc[b], 4, i % 16, 0);
+            // keeps the scheduler from hoisting later operands (registers)
+            if constexpr (i % 16 == 15) __builtin_amdgcn_sched_barrier(0);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    fp32_squares<P, fp32_group_b0(NS, NG - 1), NS>(acc, part);
 }
+
+// The lane's running minimum over the grid points of its range, and chi2 at
+// its true point.  A point's chains are folded after the next point's copies
+// have been issued; the NaN start passes no "<" and meets no true point.
+struct Fp32Min {
+    float part[4];
+    float best, cp;
+    uint32_t qbest;
+    int p;  // the universe's true point (-2: none that a grid point can meet)
+
+    __device__ __forceinline__ explicit Fp32Min(int64_t p_own)
+    {
+        part[0] = part[1] = part[2] = part[3] = cp = __builtin_nanf("");
+        best = __builtin_inff();
+        qbest = 0xffffffffu;
+        p = (p_own >= 0 && p_own < (int64_t(1) << 31)) ? (int)p_own : -2;
+    }
+    __device__ __forceinline__ void fold(int q)
+    {
+        const float chi2 = (part[0] + part[1]) + (part[2] + part[3]);
+        if (__builtin_amdgcn_ballot_w64(q == p)) cp = (q == p) ? chi2 : cp;
+        if (chi2 < best) {
+            best = chi2;
+            qbest = (uint32_t)q;
+        }
+    }
+    // merge universe u's range [qb, qe) into its state
+    __device__ __forceinline__ void merge(int64_t u, int64_t qb, int64_t qe,
+                                          unsigned long long *keys, double *chi2_p) const
+    {
+        if (p >= qb && p < qe) chi2_p[u] = (double)cp;
+        if (best < __builtin_inff())
+            atomicMin(&keys[u], ((unsigned long long)__float_as_uint(best) << 32) |
+                                    (unsigned long long)qbest);
+    }
+};
 
 // One work item (a tile of 256 universes x a range of grid points) in the
 // residual form: d - S_q is formed per bin and grid point.
 template <int N>
-__device__ __forceinline__ void fp32_item(const ScanItem &it, uint4 *buf0, uint4 *buf1)
+__device__ __forceinline__ void fp32_item(const ScanItem &it,
+                                          uint4 (&lds)[2][rec_units(n_ksteps(N))])
 {
-    constexpr int REC = rec_units(n_ksteps(N));  // A groups + 512 B of S and C
+    constexpr int NS = n_ksteps(N), NWU = rec_w_units(NS);
+    constexpr int REC = rec_units(NS);  // A groups + 512 B of S and C
     constexpr int THREADS = 64 * kWavesPerBlock;
-    static_assert(REC <= 3 * THREADS, "records of at most three 4 KB pieces");
 
     const uint4 *__restrict__ R32 = it.R;
     const double *__restrict__ d = it.d;
@@ -278,124 +206,52 @@ __device__ __forceinline__ void fp32_item(const ScanItem &it, uint4 *buf0, uint4
         L.dl[i] = (uint32_t)__builtin_bit_cast(uint16_t, lo) |
                   ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
     }
-    L.p_own = (u < K) ? (it.p_idx ? it.p_idx[u] : it.p) : -1;
-    L.best = __builtin_inff();
-    L.qbest = 0xffffffffu;
-    L.cp = 0.0f;
-    L.have_cp = false;
+    Fp32Min m((u < K) ? (it.p_idx ? it.p_idx[u] : it.p) : -1);
 
-    L.s0 = load_sig((sig_ptr)(R32 + qb * REC + rec_w_units(n_ksteps(N))), 0);
-    record_to_lds<REC, THREADS>(R32 + qb * REC, buf0, tid);
-    wait_record_loads();
-    __syncthreads();
-    // grid points in pairs so that each one's LDS buffer is fixed
-    int64_t q = qb;
-    for (; q + 1 < qe; q += 2) {
-        fp32_point<N>(q, true, R32, buf0, buf1, L);
-        fp32_point<N>(q + 1, q + 2 < qe, R32, buf1, buf0, L);
-    }
-    if (q < qe) fp32_point<N>(q, false, R32, buf0, buf1, L);
-
-    if (u < K) {
-        if (L.have_cp) it.chi2_p[u] = (double)L.cp;
-        if (L.best < __builtin_inff()) {
-            const unsigned long long key =
-                ((unsigned long long)__float_as_uint(L.best) << 32) | (unsigned long long)L.qbest;
-            atomicMin(&it.keys[u], key);
-        }
-    }
-}
-
-// Offset form for a wave whose universes all belong to one true point p
-// (Algorithm 1 runs per true point): with e = d - S_p rounded to FP32 once,
-//     W_q (d - S_q) = W_q e + T_pq,    T_pq = W_q (S_p - S_q),
-// and T_pq (FP64 arithmetic on the FP32 factor, rounded once) is the
-// accumulators' start, read from a table built before the scan.  The MFMAs
-// take e straight from registers, so the grid loop has no vector work besides
-// the squares and the minimum.
-template <int N>
-struct Fp32Fast {
-    float e[N];       // d - S_p
-    int64_t p_own;    // -1: no universe
-    float best;
-    uint32_t qbest;
-    float cp;
-    bool have_cp;
-};
-
-// Copy one offset-table row (4 ns floats, 16-byte aligned) into the wave's
-// LDS slot with direct global -> LDS loads, one 16-byte piece per lane.
-template <int NS>
-__device__ __forceinline__ void trow_to_lds(const float *__restrict__ row, float4 *dst_wave, int lane)
-{
-    if (lane < NS)
-        __builtin_amdgcn_global_load_lds((const void *)(row + 4 * lane),
-                                         (__attribute__((address_space(3))) void *)dst_wave, 16, 0,
-                                         0);
-}
-
-template <int N, int T>
-__device__ __forceinline__ void fp32_fast_pair(v4f (&acc)[n_ksteps(N)], float4 &a_cur, float4 &a_nxt,
-                                               const Fp32Fast<N> &L, const float4 *__restrict__ wl,
-                                               int lane)
-{
-    constexpr int NS = n_ksteps(N), P = fp32_pad(NS, N);
-    constexpr int KP = fp32_pair_kp(NS, T), B = fp32_pair_b(NS, T);
-    constexpr int V = T / 16, NG = n_groups_from_ns(NS);
-    if constexpr (T % 64 == 0 && T > 0) {
-        a_cur = a_nxt;
-        if constexpr (T / 64 + 1 < NG) a_nxt = wl[(T / 64 + 1) * 64 + lane];
-    }
-    if constexpr (KP >= P) {
-        acc[B] = __builtin_amdgcn_mfma_f32_4x4x1f32(pick(a_cur, V % 4), L.e[KP - P], acc[B], 4,
-                                                    T % 16, 0);
-        if constexpr (B == NS - 1 && (KP - P) % 8 == 7) __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-template <int N, int... Ts>
-__device__ __forceinline__ void fp32_fast_pairs(v4f (&acc)[n_ksteps(N)], float4 &a_cur,
-                                                float4 &a_nxt, const Fp32Fast<N> &L,
-                                                const float4 *__restrict__ wl, int lane,
-                                                std::integer_sequence<int, Ts...>)
-{
-    (fp32_fast_pair<N, Ts>(acc, a_cur, a_nxt, L, wl, lane), ...);
-}
-
-template <int N>
-__device__ __forceinline__ void fp32_fast_point(int64_t q, bool more, const uint4 *__restrict__ R32,
-                                                const float *__restrict__ trow_q, const uint4 *cur,
-                                                uint4 *nxt, const float4 *tcur, float4 *tnxt,
-                                                Fp32Fast<N> &L)
-{
-    constexpr int NS = n_ksteps(N), P = fp32_pad(NS, N);
-    constexpr int REC = rec_units(NS);
-    constexpr int NR = 4 * NS;
-    constexpr int THREADS = kPtsTile;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-
-    if (more) {
-        record_to_lds<REC, THREADS>(R32 + (q + 1) * REC, nxt, tid);
-        if (tid < 64) trow_to_lds<NS>(trow_q + NR, tnxt, lane);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-
-    const float4 *wl = reinterpret_cast<const float4 *>(cur);
-    v4f acc[NS];
+    const int lane = tid & 63, wbase = __builtin_amdgcn_readfirstlane(tid & ~63);
+    record_to_lds_sbase<REC, THREADS>(R32 + qb * REC, lds[0], tid, wbase);
+    const int qei = (int)qe;
+    // (restrict: the reads of `cur` need not wait for the loads into `nxt`)
+    const auto point = [&](int q, const uint4 *__restrict__ cur, uint4 *__restrict__ nxt) {
+        // the packed FP16 parts are re-presented to the compiler at every grid
+        // point, so that their FP32 conversions stay inside the mixed FMAs
+        // instead of being hoisted out of the grid loop into extra registers
 #pragma unroll
-    for (int b = 0; b < NS; ++b) {
-        const float4 tv = tcur[b];
-        acc[b] = v4f{tv.x, tv.y, tv.z, tv.w};
-    }
-    float4 a_cur = wl[lane], a_nxt = a_cur;
-    if constexpr (n_groups_from_ns(NS) > 1) a_nxt = wl[64 + lane];
-    fp32_fast_pairs<N>(acc, a_cur, a_nxt, L, wl, lane,
-                       std::make_integer_sequence<int, fp32_npairs(NS)>{});
-    fp32_fold<NS, P>(acc, q, L.p_own, L.best, L.qbest, L.cp, L.have_cp);
-
-    if (more) wait_record_loads();
-    __syncthreads();
+        for (int i = 0; i < (N + 1) / 2; ++i) asm volatile("" : "+v"(L.dl[i]));
+        wait_record_loads();
+        __syncthreads();  // record q is in cur; every wave is done with nxt
+        if (q + 1 < qei)
+            record_to_lds_sbase<REC, THREADS>(R32 + (int64_t)(q + 1) * REC, nxt, tid, wbase);
+        __builtin_amdgcn_sched_barrier(0);
+        m.fold(q - 1);
+        // the residuals of every bin in one phase, the signal's FP32 part from
+        // LDS (uniform reads, kAhead of four bins ahead; through the scalar
+        // cache they would make the LDS reads wait for the scalar loads)
+        constexpr int kAhead = 4;
+        const float4 *sg = reinterpret_cast<const float4 *>(cur + NWU);
+        float r[N];
+        float4 s[NS];
+        static_for<0, (kAhead < NS ? kAhead : NS)>([&](auto xc) {
+            constexpr int x = decltype(xc)::value;
+            s[x] = sg[x];
+        });
+        static_for<0, NS>([&](auto xc) {
+            constexpr int x = decltype(xc)::value;
+            if constexpr (x + kAhead < NS) s[x + kAhead] = sg[x + kAhead];
+            static_for<4 * x, (4 * x + 4 < N ? 4 * x + 4 : N)>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                r[k] = fma_mix_dl<k & 1>(L.dl[k / 2], L.dl_scale, L.dh[k] - pick(s[x], k % 4));
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        // accumulators start at C_q (the same four rows in every lane)
+        fp32_contract<N>(reinterpret_cast<const float4 *>(cur) + lane,
+                         reinterpret_cast<const float4 *>(cur + NWU) + 16, r, m.part);
+    };
+    int buf = 0;
+    for (int q = (int)qb; q < qei; ++q, buf ^= 1) point(q, lds[buf], lds[buf ^ 1]);
+    m.fold(qei - 1);
+    if (u < K) m.merge(u, qb, qe, it.keys, it.chi2_p);
 }
 
 template <int N>
@@ -404,7 +260,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int64_t *__restrict__ p_idx, int64_t K, int64_t q_lo, int64_t q_hi, int64_t n_utiles,
     int64_t q_per_chunk, unsigned long long *__restrict__ keys, double *__restrict__ chi2_p)
 {
-    __shared__ uint4 buf0[rec_units(n_ksteps(N))], buf1[rec_units(n_ksteps(N))];
+    __shared__ uint4 lds[2][rec_units(n_ksteps(N))];
     ScanItem it;
     it.R = R32;
     it.d = d;
@@ -421,7 +277,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     it.u0 = utile * (int64_t)kFp32UnivPerBlock;
     it.qb = q_lo + qchunk * q_per_chunk;
     it.qe = (it.qb + q_per_chunk < q_hi) ? it.qb + q_per_chunk : q_hi;
-    fp32_item<N>(it, buf0, buf1);
+    fp32_item<N>(it, lds);
 }
 
 // Serving: a persistent-style launch over a table of items (any mix of
@@ -432,7 +288,7 @@ template <int N>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_serve_fp32(
     const ScanItem *__restrict__ items, int n_items, int *__restrict__ counter)
 {
-    __shared__ uint4 buf0[rec_units(n_ksteps(N))], buf1[rec_units(n_ksteps(N))];
+    __shared__ uint4 lds[2][rec_units(n_ksteps(N))];
     __shared__ int cur;
     for (;;) {
         if (threadIdx.x == 0) cur = atomicAdd(counter, 1);
@@ -440,12 +296,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         const int i = cur;
         __syncthreads();
         if (i >= n_items) break;
-        fp32_item<N>(items[i], buf0, buf1);
+        fp32_item<N>(items[i], lds);
         __syncthreads();
     }
 }
 
-// Scan of universes grouped by true point, offset form throughout.  Tiles of
+// Scan of universes grouped by true point, in the offset form: with
+// e = d - S_p rounded to FP32 once,
+//     W_q (d - S_q) = W_q e + T_pq,    T_pq = W_q (S_p - S_q),
+// and T_pq (FP64 arithmetic on the FP32 factor, rounded once) is the
+// accumulators' start, read from a table built before the scan.  The MFMAs
+// take e straight from registers, so the grid loop has no vector work besides
+// the squares and the minimum.  Tiles of
 // B = kPtsTile universes never straddle segments: segment s owns the dense
 // tile ids [tile_start[s], tile_start[s+1]), tile_start[s+1] - tile_start[s] =
 // ceil(len_s / B) (a prefix sum built before the launch), all below
@@ -460,7 +322,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // when the grid is split over several launches or devices.  Segments whose
 // true point is outside the grid do nothing.
 template <int N>
-__global__ __launch_bounds__(kPtsTile) __attribute__((amdgpu_waves_per_eu(2))) void k_scan_fp32_pts(
+__global__ __launch_bounds__(kPtsTile) __attribute__((amdgpu_waves_per_eu(3))) void k_scan_fp32_pts(
     const uint4 *__restrict__ R32, const double *__restrict__ S64, const double *__restrict__ d,
     int64_t G, int64_t n_pts, const int64_t *__restrict__ p, const int64_t *__restrict__ seg_off,
     const int64_t *__restrict__ tile_start, const float *__restrict__ T, int64_t groups_per_xcd,
@@ -471,8 +333,7 @@ __global__ __launch_bounds__(kPtsTile) __attribute__((amdgpu_waves_per_eu(2))) v
     constexpr int REC = rec_units(NS);
     constexpr int NR = 4 * NS;
     constexpr int THREADS = kPtsTile;
-    __shared__ uint4 buf0[REC], buf1[REC];
-    __shared__ float4 tb0[16], tb1[16];
+    __shared__ uint4 lds[2][REC], tb[2][16];
     const int64_t b = blockIdx.x;
     const int64_t xcd = b % 8, k = b / 8;
     const int64_t member = k % 8, rest = k / 8;
@@ -497,42 +358,49 @@ __global__ __launch_bounds__(kPtsTile) __attribute__((amdgpu_waves_per_eu(2))) v
     if (qb >= qe || pp < 0 || pp >= G) return;  // uniform per block
     const int tid = threadIdx.x;
     const int lane = tid & 63;
+    const int wbase = __builtin_amdgcn_readfirstlane(tid & ~63);
     const int64_t u = s0 + kPtsTile * i + tid;
     // (the row must also lie in [0, K): offsets that break their contract
     // read and write nothing outside the arrays)
     const bool act = u < s1 && u >= 0 && u < K;
 
-    Fp32Fast<N> L;
-    const double *__restrict__ sp = S64 + pp * N;  // uniform: scalar loads
-#pragma unroll
-    for (int k = 0; k < N; ++k) L.e[k] = act ? (float)(d[u * N + k] - sp[k]) : 0.0f;
-    L.p_own = act ? pp : -1;
-    L.best = __builtin_inff();
-    L.qbest = 0xffffffffu;
-    L.cp = 0.0f;
-    L.have_cp = false;
-    // offset rows of this segment: one per grid point of [q_lo, q_hi)
+    // offset rows of this segment, one of 4 ns floats per grid point of
+    // [q_lo, q_hi); the block's first wave copies them beside the records
     const float *__restrict__ trow = T + (seg * (q_hi - q_lo) + (qb - q_lo)) * NR;
-
-    record_to_lds<REC, THREADS>(R32 + qb * REC, buf0, tid);
-    if (tid < 64) trow_to_lds<NS>(trow, tb0, lane);
-    wait_record_loads();
-    __syncthreads();
-    int64_t q = qb;
-    for (; q + 1 < qe; q += 2, trow += 2 * NR) {
-        fp32_fast_point<N>(q, true, R32, trow, buf0, buf1, tb0, tb1, L);
-        fp32_fast_point<N>(q + 1, q + 2 < qe, R32, trow + NR, buf1, buf0, tb1, tb0, L);
-    }
-    if (q < qe) fp32_fast_point<N>(q, false, R32, trow, buf0, buf1, tb0, tb1, L);
-
-    if (act) {
-        if (L.have_cp) chi2_p[u] = (double)L.cp;
-        if (L.best < __builtin_inff()) {
-            const unsigned long long key =
-                ((unsigned long long)__float_as_uint(L.best) << 32) | (unsigned long long)L.qbest;
-            atomicMin(&keys[u], key);
+    record_to_lds_sbase<REC, THREADS>(R32 + qb * REC, lds[0], tid, wbase);
+    if (wbase == 0)
+        record_to_lds_sbase<NS, 64>(reinterpret_cast<const uint4 *>(trow), tb[0], lane, 0);
+    const double *__restrict__ sp = S64 + pp * N;  // uniform: scalar loads
+    float e[N];
+    static_for<0, N>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        e[k] = act ? (float)(d[u * N + k] - sp[k]) : 0.0f;
+        if constexpr (k % 16 == 15) __builtin_amdgcn_sched_barrier(0);  // 16 loads in flight
+    });
+    Fp32Min m(act ? pp : -1);
+    const int qei = (int)qe;
+    // (restrict: the reads of `cur` and `tcur` need not wait for the loads
+    // into the other buffers)
+    const auto point = [&](int q, const uint4 *__restrict__ cur, uint4 *__restrict__ nxt,
+                           const uint4 *__restrict__ tcur, uint4 *__restrict__ tnxt) {
+        wait_record_loads();
+        __syncthreads();  // record q is in cur; every wave is done with nxt
+        trow += NR;
+        if (q + 1 < qei) {
+            record_to_lds_sbase<REC, THREADS>(R32 + (int64_t)(q + 1) * REC, nxt, tid, wbase);
+            if (wbase == 0)
+                record_to_lds_sbase<NS, 64>(reinterpret_cast<const uint4 *>(trow), tnxt, lane, 0);
         }
-    }
+        __builtin_amdgcn_sched_barrier(0);
+        m.fold(q - 1);
+        fp32_contract<N>(reinterpret_cast<const float4 *>(cur) + lane,
+                         reinterpret_cast<const float4 *>(tcur), e, m.part);
+    };
+    int buf = 0;
+    for (int q = (int)qb; q < qei; ++q, buf ^= 1)
+        point(q, lds[buf], lds[buf ^ 1], tb[buf], tb[buf ^ 1]);
+    m.fold(qei - 1);
+    if (act) m.merge(u, qb, qe, keys, chi2_p);
 }
 
 __global__ __launch_bounds__(256) void k_init_keys(int64_t K, unsigned long long *__restrict__ keys,
@@ -730,12 +598,15 @@ __global__ __launch_bounds__(256) void k_offset_table(const uint4 *__restrict__ 
     __shared__ unsigned char pk[NP], pb[NP];
     const int tid = threadIdx.x;
     if (tid == 0) {
-        int t = 0;
-        for (int kp = 0; kp < NR; ++kp)
-            for (int b = kp / 4; b < NS; ++b, ++t) {
-                pk[t] = (unsigned char)kp;
-                pb[t] = (unsigned char)b;
-            }
+        int t = 0;  // position in the record
+        for (int g = 0; g < fp32_ngroup(NS); ++g) {
+            const int b0 = fp32_group_b0(NS, g), b1 = fp32_group_b0(NS, g + 1);
+            for (int kp = 0; kp < 4 * b1; ++kp)
+                for (int b = max(kp / 4, b0); b < b1; ++b, ++t) {
+                    pk[t] = (unsigned char)kp;
+                    pb[t] = (unsigned char)b;
+                }
+        }
     }
     __syncthreads();
     float *wt = reinterpret_cast<float *>(Wt);
