@@ -475,6 +475,7 @@ struct fc_grid {
     double *F64 = nullptr;  // device [N][N] fractional covariance of the last build
     double *LF64 = nullptr; // device [N][N] its Cholesky factor (universe generation)
     int lf_ok = 0;          // 1 if F is positive definite (LF64 valid)
+    char *build_ws = nullptr;  // device workspace of the covariance build
     size_t bytes = 0;
     int ns = 0, ng = 0;     // FP32 fragment geometry
 };
