@@ -4,9 +4,19 @@
 // left of which that fraction of the Delta chi^2 distribution lies.  It is
 // taken as the type-1 order statistic x_(j), j = ceil(alpha K) clamped to
 // [1, K], with NaN ordered last.  One block per segment finds x_(j) for every
-// alpha at once by an 8-pass radix select (8 bits per pass) over 64-bit keys
-// whose unsigned order is the numeric order of the doubles; no sort, no
-// scratch memory beyond LDS counters.
+// alpha over 64-bit keys whose unsigned order is the numeric order of the
+// doubles: the keys between the segment's smallest and largest are counted in
+// 2^BITS equal intervals, each rank's interval is cut again until it holds at
+// most kCand keys (one or two cuts: the intervals of the first already split
+// the range the values occupy, where a fixed radix spends its first digits on
+// the sign and exponent they share and its counters on one address), and those
+// are ranked directly.  No sort, no scratch memory beyond LDS; the first
+// KR T keys stay in registers between the passes.
+//
+// Bound: latency of one block (loads, LDS atomics, a barrier per pass).  With
+// three alphas and a 200-bin histogram, one segment of 1000 / 5000 / 20 000
+// values takes 11 / 23 / 45 us; the 8-pass radix select of 256 threads that
+// this replaced took 23 / 89 / 273 us.
 #include "fc_internal.h"
 
 namespace fcx {
@@ -31,113 +41,227 @@ __device__ __forceinline__ double from_order_key(unsigned long long k)
     return __longlong_as_double((long long)b);
 }
 
+constexpr int kCand = 256;  // keys ranked directly
+
 // Segment s is x[seg_lo[s] .. seg_hi[s]).  The order statistics taken are
 // ranks ceil(alpha K) (alpha mode), or ranks[s][a] (1-based, clamped to
 // [1, K]) when a rank table is given.
-__global__ __launch_bounds__(256) void k_crit(const int64_t *__restrict__ seg_lo,
-                                             const int64_t *__restrict__ seg_hi,
-                                             const double *__restrict__ x, int n_alpha,
-                                             AlphaArgs alpha, const int64_t *__restrict__ ranks,
-                                             double *__restrict__ crit, int n_bins,
-                                             double hist_hi, int64_t *__restrict__ hist)
+template <int T, int BITS, int KR>
+__global__ __launch_bounds__(T) void k_crit(const int64_t *__restrict__ seg_lo,
+                                            const int64_t *__restrict__ seg_hi,
+                                            const double *__restrict__ x, int n_alpha,
+                                            AlphaArgs alpha, const int64_t *__restrict__ ranks,
+                                            double *__restrict__ crit, int n_bins, double hist_hi,
+                                            int64_t *__restrict__ hist)
 {
-    __shared__ unsigned int cnt[kMaxAlpha][256];
-    __shared__ unsigned long long prefix[kMaxAlpha];
-    __shared__ long long rank[kMaxAlpha];
+    constexpr int BINS = 1 << BITS, NW = T / 64;
+    static_assert(BINS % 64 == 0 && kMaxAlpha * BINS * 4 >= kMaxAlpha * kCand * 8, "LDS sharing");
+    // counters of every rank's interval, then its remaining keys
+    __shared__ union {
+        unsigned int cnt[kMaxAlpha][BINS];
+        unsigned long long cand[kMaxAlpha][kCand];
+    } sh;
+    __shared__ unsigned long long lo_s[kMaxAlpha], red[2][NW];
+    __shared__ long long rank_s[kMaxAlpha];
+    __shared__ unsigned int num_s[kMaxAlpha], fill_s[kMaxAlpha];
+    __shared__ int shift_s[kMaxAlpha];
     extern __shared__ unsigned int hbin[];
 
     const int64_t sgi = blockIdx.x;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int64_t lo = seg_lo[sgi], hi = seg_hi[sgi];
     const bool valid = lo >= 0 && hi >= lo;
     const int64_t K = valid ? hi - lo : 0;
 
-    // ---- histogram ----------------------------------------------------------
     if (hist) {
-        for (int b = tid; b <= n_bins; b += blockDim.x) hbin[b] = 0u;
+        for (int b = tid; b <= n_bins; b += T) hbin[b] = 0u;
         __syncthreads();
-        const double width = hist_hi / (double)n_bins;
-        for (int64_t k = tid; k < K; k += blockDim.x) {
-            const double v = x[lo + k];
-            int b = n_bins;
-            if (v >= 0.0 && v < hist_hi) {
-                const double f = floor(v / width);
-                b = (f > (double)(n_bins - 1)) ? n_bins - 1 : (int)f;
-            }
-            atomicAdd(&hbin[b], 1u);
-        }
-        __syncthreads();
-        for (int b = tid; b <= n_bins; b += blockDim.x)
-            hist[sgi * (int64_t)(n_bins + 1) + b] = (int64_t)hbin[b];
     }
-
-    // ---- radix select --------------------------------------------------------
+    const double width = hist ? hist_hi / (double)n_bins : 1.0;
+    const auto count = [&](double v) {
+        int b = n_bins;
+        if (v >= 0.0 && v < hist_hi) {
+            const double f = floor(v / width);
+            b = (f > (double)(n_bins - 1)) ? n_bins - 1 : (int)f;
+        }
+        atomicAdd(&hbin[b], 1u);
+    };
+    // one pass over the values: histogram, smallest and largest key
+    unsigned long long key[KR], kmin = ~0ull, kmax = 0ull;
+    const auto first = [&](double v) {
+        if (hist) count(v);
+        const unsigned long long k = order_key(v);
+        kmin = k < kmin ? k : kmin;
+        kmax = k > kmax ? k : kmax;
+        return k;
+    };
+    if (K > 0) {
+        double v[KR];  // the loads first (clamped to the segment), then their use
+#pragma unroll
+        for (int i = 0; i < KR; ++i)
+            if ((int64_t)i * T < K) v[i] = x[lo + (i * T + tid < K ? i * T + tid : K - 1)];
+#pragma unroll
+        for (int i = 0; i < KR; ++i)
+            if (i * T + tid < K) key[i] = first(v[i]);
+    }
+    for (int64_t k = (int64_t)KR * T + tid; k < K; k += T) (void)first(x[lo + k]);
+    // later passes: fn(key) for every key of the segment
+    const auto each = [&](auto fn) {
+#pragma unroll
+        for (int i = 0; i < KR; ++i)
+            if (i * T + tid < K) fn(key[i]);
+        for (int64_t k = (int64_t)KR * T + tid; k < K; k += T) fn(order_key(x[lo + k]));
+    };
     if (K == 0) {
+        if (hist)
+            for (int b = tid; b <= n_bins; b += T) hist[sgi * (int64_t)(n_bins + 1) + b] = 0;
         if (tid < n_alpha) crit[sgi * n_alpha + tid] = __builtin_nan("");
         return;
     }
+    for (int m = 32; m > 0; m >>= 1) {
+        const unsigned long long a = __shfl_xor(kmin, m), b = __shfl_xor(kmax, m);
+        kmin = a < kmin ? a : kmin;
+        kmax = b > kmax ? b : kmax;
+    }
+    if (lane == 0) {
+        red[0][wave] = kmin;
+        red[1][wave] = kmax;
+    }
+    for (int e = tid; e < BINS; e += T) sh.cnt[0][e] = 0u;
+    __syncthreads();
+    if (hist)
+        for (int b = tid; b <= n_bins; b += T)
+            hist[sgi * (int64_t)(n_bins + 1) + b] = (int64_t)hbin[b];
+    for (int w = 0; w < NW; ++w) {
+        kmin = red[0][w] < kmin ? red[0][w] : kmin;
+        kmax = red[1][w] > kmax ? red[1][w] : kmax;
+    }
+    // 2^s keys an interval, the fewest that leave 2^BITS intervals
+    const unsigned long long span = kmax - kmin;
+    const int s0 = (span >> BITS) ? 64 - BITS - __builtin_clzll(span) : 0;
     if (tid < n_alpha) {
         long long j = ranks ? (long long)ranks[sgi * n_alpha + tid]
                             : (long long)ceil(alpha.a[tid] * (double)K);
         if (j < 1) j = 1;
         if (j > K) j = K;
-        rank[tid] = j - 1;  // 0-based
-        prefix[tid] = 0ull;
+        rank_s[tid] = j - 1;  // 0-based
+        lo_s[tid] = kmin;
+        shift_s[tid] = s0;
+        num_s[tid] = (unsigned int)K;
+        fill_s[tid] = 0u;
+    }
+    // interval of rank rank_s[a] in table t: wave a, lane l holding bins
+    // l BINS/64 ..., a prefix sum over the lanes finds the lane that covers it
+    const auto pick = [&](int a, int t, int s) {  // table t's intervals: 2^s keys each
+        constexpr int PER = BINS / 64;
+        const long long r = rank_s[a];
+        long long own = 0;
+        for (int e = 0; e < PER; ++e) own += sh.cnt[t][lane * PER + e];
+        long long incl = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const long long up = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += up;
+        }
+        if (incl - own <= r && r < incl) {
+            long long rr = r - (incl - own);
+            int e = lane * PER;
+            while (rr >= sh.cnt[t][e]) rr -= sh.cnt[t][e++];
+            rank_s[a] = rr;
+            num_s[a] = sh.cnt[t][e];
+            lo_s[a] += (unsigned long long)e << s;
+            shift_s[a] = s;
+        }
+    };
+    if (K > kCand) {
+        // the first cut is the same for every rank
+        each([&](unsigned long long k) { atomicAdd(&sh.cnt[0][(k - kmin) >> s0], 1u); });
+        __syncthreads();
+        for (int a = wave; a < n_alpha; a += NW) pick(a, 0, s0);
+        for (;;) {
+            __syncthreads();
+            bool more = false;
+            for (int a = 0; a < n_alpha; ++a)
+                more = more || (shift_s[a] > 0 && num_s[a] > (unsigned)kCand);
+            if (!more) break;  // uniform
+            for (int e = tid; e < n_alpha * BINS; e += T) (&sh.cnt[0][0])[e] = 0u;
+            __syncthreads();
+            each([&](unsigned long long k) {
+                for (int a = 0; a < n_alpha; ++a) {
+                    const int s = shift_s[a];
+                    if (s > 0 && num_s[a] > (unsigned)kCand && k >= lo_s[a] &&
+                        ((k - lo_s[a]) >> s) == 0)
+                        atomicAdd(&sh.cnt[a][(k - lo_s[a]) >> (s > BITS ? s - BITS : 0)], 1u);
+                }
+            });
+            __syncthreads();
+            for (int a = wave; a < n_alpha; a += NW)
+                if (shift_s[a] > 0 && num_s[a] > (unsigned)kCand)
+                    pick(a, a, shift_s[a] > BITS ? shift_s[a] - BITS : 0);
+        }
     }
     __syncthreads();
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        for (int e = tid; e < kMaxAlpha * 256; e += blockDim.x) (&cnt[0][0])[e] = 0u;
+    // keys below `own` among the first n of a list, equal ones by position
+    const auto below = [&](const unsigned long long *list, int n, int i) {
+        const unsigned long long own = list[i];
+        int b = 0;
+#pragma unroll 8
+        for (int c = 0; c < n; ++c) b += (list[c] < own || (list[c] == own && c < i)) ? 1 : 0;
+        return b;
+    };
+    if (K <= kCand) {
+        // every key's rank, once for all alphas
+        each([&](unsigned long long k) { sh.cand[0][atomicAdd(&fill_s[0], 1u)] = k; });
         __syncthreads();
-        const unsigned long long himask = (shift == 56) ? 0ull : (~0ull << (shift + 8));
-        for (int64_t k = tid; k < K; k += blockDim.x) {
-            const unsigned long long key = order_key(x[lo + k]);
-            const unsigned int digit = (unsigned int)((key >> shift) & 255ull);
+        for (int i = tid; i < (int)K; i += T) {
+            const int r = below(sh.cand[0], (int)K, i);
             for (int a = 0; a < n_alpha; ++a)
-                if ((key & himask) == prefix[a]) atomicAdd(&cnt[a][digit], 1u);
+                if (r == (int)rank_s[a])
+                    crit[sgi * n_alpha + a] = from_order_key(sh.cand[0][i]);
         }
-        __syncthreads();
-        // digit of rank r: one wave per fraction, lane l holding digits 4l..4l+3;
-        // a prefix sum over the lanes finds the lane whose digits cover r
-        const int wave = tid >> 6, lane = tid & 63;
-        for (int a = wave; a < n_alpha; a += 4) {
-            const long long r = rank[a];
-            const long long c0 = cnt[a][4 * lane], c1 = cnt[a][4 * lane + 1],
-                            c2 = cnt[a][4 * lane + 2], c3 = cnt[a][4 * lane + 3];
-            const long long own = c0 + c1 + c2 + c3;
-            long long incl = own;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const long long up = __shfl_up(incl, off, 64);
-                if (lane >= off) incl += up;
-            }
-            const long long excl = incl - own;
-            const long long total = __shfl(incl, 63, 64);
-            if (excl <= r && r < incl) {
-                long long rr = r - excl;
-                unsigned int d = 4 * lane;
-                if (rr >= c0) {
-                    rr -= c0;
-                    ++d;
-                    if (rr >= c1) {
-                        rr -= c1;
-                        ++d;
-                        if (rr >= c2) {
-                            rr -= c2;
-                            ++d;
-                        }
-                    }
-                }
-                rank[a] = rr;
-                prefix[a] |= ((unsigned long long)d) << shift;
-            } else if (lane == 63 && r >= total) {  // not reached for a consistent count
-                rank[a] = r - total;
-                prefix[a] |= 255ull << shift;
-            }
-        }
-        __syncthreads();
+        return;
     }
-    if (tid < n_alpha) crit[sgi * n_alpha + tid] = from_order_key(prefix[tid]);
+    // the keys of every rank's interval, and the one of that rank among them
+    // (an interval of one key value needs none)
+    each([&](unsigned long long k) {
+        for (int a = 0; a < n_alpha; ++a) {
+            const int s = shift_s[a];
+            if (s > 0 && k >= lo_s[a] && ((k - lo_s[a]) >> s) == 0)
+                sh.cand[a][atomicAdd(&fill_s[a], 1u)] = k;
+        }
+    });
+    __syncthreads();
+    for (int e = tid; e < n_alpha * kCand; e += T) {
+        const int a = e / kCand, i = e % kCand, n = (int)fill_s[a];
+        if (shift_s[a] == 0) {
+            if (i == 0) crit[sgi * n_alpha + a] = from_order_key(lo_s[a]);
+        } else if (i < n) {
+            if (below(sh.cand[a], n, i) == (int)rank_s[a])
+                crit[sgi * n_alpha + a] = from_order_key(sh.cand[a][i]);
+        }
+    }
 }
+
+namespace {
+
+// Few segments: 1024 threads each, since a block's own latency is the time;
+// many: 256, so that several share a CU (1600 segments of 128-2048 values).
+hipError_t launch_crit_any(int64_t n_seg, const int64_t *seg_lo, const int64_t *seg_hi,
+                           const double *x, int n_alpha, const AlphaArgs &aa,
+                           const int64_t *ranks, double *crit, int n_bins, double hist_hi,
+                           int64_t *hist, hipStream_t st)
+{
+    const size_t lds = hist ? sizeof(unsigned int) * (size_t)(n_bins + 1) : 0;
+    if (n_seg <= 512)
+        hipLaunchKernelGGL((k_crit<1024, 10, 20>), dim3((unsigned)n_seg), dim3(1024), lds, st,
+                           seg_lo, seg_hi, x, n_alpha, aa, ranks, crit, n_bins, hist_hi, hist);
+    else
+        hipLaunchKernelGGL((k_crit<256, 9, 10>), dim3((unsigned)n_seg), dim3(256), lds, st, seg_lo,
+                           seg_hi, x, n_alpha, aa, ranks, crit, n_bins, hist_hi, hist);
+    return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t launch_crit(int64_t n_seg, const int64_t *seg_off, const double *x, int n_alpha,
                        const double *alpha, double *crit, int n_bins, double hist_hi,
@@ -145,10 +269,8 @@ hipError_t launch_crit(int64_t n_seg, const int64_t *seg_off, const double *x, i
 {
     AlphaArgs aa;
     for (int a = 0; a < kMaxAlpha; ++a) aa.a[a] = (a < n_alpha) ? alpha[a] : 1.0;
-    const size_t lds = hist ? sizeof(unsigned int) * (size_t)(n_bins + 1) : 0;
-    hipLaunchKernelGGL(k_crit, dim3((unsigned)n_seg), dim3(256), lds, st, seg_off, seg_off + 1, x,
-                       n_alpha, aa, nullptr, crit, n_bins, hist_hi, hist);
-    return hipGetLastError();
+    return launch_crit_any(n_seg, seg_off, seg_off + 1, x, n_alpha, aa, nullptr, crit, n_bins,
+                           hist_hi, hist, st);
 }
 
 hipError_t launch_crit_gapped(int64_t n_seg, const int64_t *seg_lo, const int64_t *seg_hi,
@@ -157,9 +279,8 @@ hipError_t launch_crit_gapped(int64_t n_seg, const int64_t *seg_lo, const int64_
 {
     AlphaArgs aa;
     for (int a = 0; a < kMaxAlpha; ++a) aa.a[a] = (a < n_alpha) ? alpha[a] : 1.0;
-    hipLaunchKernelGGL(k_crit, dim3((unsigned)n_seg), dim3(256), 0, st, seg_lo, seg_hi, x, n_alpha,
-                       aa, nullptr, crit, 0, 1.0, nullptr);
-    return hipGetLastError();
+    return launch_crit_any(n_seg, seg_lo, seg_hi, x, n_alpha, aa, nullptr, crit, 0, 1.0, nullptr,
+                           st);
 }
 
 hipError_t launch_select_ranks(int64_t n_seg, const int64_t *seg_lo, const int64_t *seg_hi,
@@ -168,9 +289,7 @@ hipError_t launch_select_ranks(int64_t n_seg, const int64_t *seg_lo, const int64
 {
     AlphaArgs aa;
     for (int a = 0; a < kMaxAlpha; ++a) aa.a[a] = 1.0;
-    hipLaunchKernelGGL(k_crit, dim3((unsigned)n_seg), dim3(256), 0, st, seg_lo, seg_hi, x, n_q, aa,
-                       ranks, out, 0, 1.0, nullptr);
-    return hipGetLastError();
+    return launch_crit_any(n_seg, seg_lo, seg_hi, x, n_q, aa, ranks, out, 0, 1.0, nullptr, st);
 }
 
 }  // namespace fcx
