@@ -272,8 +272,9 @@ k_scan_f64m(const uint4 *__restrict__ R64, const double *__restrict__ d,
 // chunks partition the grid in order, so that is the earlier chunk, and the
 // result is the sequential scan's.  Chunk values are never NaN (a NaN chi2
 // never passes "<"), and a chunk with no finite value reports (+inf, p).  A
-// true point outside [0, G) was owned by no chunk: chi2_p = NaN.  chi2_min
-// and argmin may be nullptr; chi2_p holds the owners' values on entry.
+// true point outside [0, G) was owned by no chunk: chi2_p = NaN, whatever its
+// element holds.  chi2_min and argmin may be nullptr; chi2_p holds the owners'
+// values on entry.
 __global__ __launch_bounds__(256) void k_fp64_merge(const Fp64Part *__restrict__ part,
                                                    int64_t n_chunks, const int64_t *__restrict__ p_idx,
                                                    int64_t K, int64_t G, double *__restrict__ dchi2,
@@ -309,14 +310,6 @@ __global__ __launch_bounds__(256) void k_fp64_merge(const Fp64Part *__restrict__
     if (argmin) argmin[u] = qbest;
     chi2_p[u] = cp;
     dchi2[u] = cp - best;
-}
-
-// Initial chi2_p of a chunked scan: NaN for universes whose true point no
-// chunk owns.
-__global__ __launch_bounds__(256) void k_fill_nan(int64_t K, double *__restrict__ x)
-{
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u < K) x[u] = __builtin_nan("");
 }
 
 namespace {
@@ -357,9 +350,6 @@ hipError_t launch_f64m_n(const fc_grid *g, int64_t K, const double *d, const int
         qpc = G;
     }
     const int64_t blocks = sg.n_utiles * chunks;
-    if (part)
-        hipLaunchKernelGGL(k_fill_nan, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, K,
-                           chi2_p);
     {
         ProfScope prof(st, "k_scan_f64m");
         hipLaunchKernelGGL(k_scan_f64m<N>, dim3((unsigned)blocks), dim3(64 * kF64Waves), 0, st,
