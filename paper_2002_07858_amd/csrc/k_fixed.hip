@@ -24,6 +24,18 @@
 // points per step against the block's universes, whose y fragments stay in
 // registers; the t tile (64 points x 4*NS bins) is double-buffered in LDS and
 // brought in by direct global -> LDS loads while the previous tile is used.
+//
+// Groups of at most kFxSmall universes (almost all of them once the matrices
+// are those of the minimisers) would leave much of that tile empty and write
+// and read a whole t table for a few universes.  k_fixed_small forms t_q on
+// the fly instead: with W_m as the A operand, t^T = W_m X^T comes out of the
+// matrix cores in exactly the layout of the B operand of y t^T, so t is never
+// stored, and only the steps on or below the diagonal are issued (39 of 60 at
+// N = 57).  Per 16 grid points: 54 MFMAs for a tile of 16 universes, 69 for one
+// of 32, against 60 for t, a write and a read of t, and 60 for each tile of 64.
+// Same sums in the same order.  100 x 100 points, N = 57, 16 x 2000 universes
+// iterated: 41.4 -> 13.4 ms.  Bound: FP64 matrix rate and the rounds' tails.
+//
 // Per-chunk minima (value, q) are merged by a small kernel with Algorithm 1's
 // rule (smallest value, then lowest q).
 #include "fc_internal.h"
@@ -37,6 +49,12 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kFxTile = 64;      // universes per block, grid points per step
 constexpr int kFxThreads = 256;
+// Groups up to this size go to k_fixed_small; larger ones share a t table
+// (64 groups of n universes, 10 000 points, N = 57, the whole call, the best of
+// three: n = 128 0.67 ms against 0.92 with tables, 192 0.92 against 1.07, 256
+// 1.11 against 2.95, 512 2.03 against 1.73; N = 20 on 3600 points: 128 0.24
+// against 0.26, 256 0.39 against 0.37).
+constexpr int kFxSmall = 256;
 
 // y = W_m (d - o), a = ||y||^2 for universe rows in group order: one wave per
 // row, lane i = component i (zero past N, stored padded to 4 * ns).
@@ -128,20 +146,216 @@ __global__ __launch_bounds__(256) void k_fixed_t(const double *__restrict__ W64,
 
 struct FxTileDesc {
     int64_t r0;     // first row (group order) of the tile
-    int32_t n;      // rows in the tile (1..64)
-    int32_t slot;   // matrix slot of the group
+    int32_t n;      // rows in the tile (1..64; k_fixed_small: 1..16 NU)
+    int32_t slot;   // matrix slot of the group (k_fixed_small: the matrix's grid point)
 };
 
+// X = S - o in the B-operand order of k_fixed_small: Xt[q / 16][s][lane] holds
+// grid point q = 16 (q / 16) + lane % 16, bin 4 s + lane / 16 (zero past G and N).
+__global__ __launch_bounds__(256) void k_fixed_x(const double *__restrict__ S64,
+                                                 const double *__restrict__ off, int N, int ns,
+                                                 int64_t G, int64_t n, double *__restrict__ Xt)
+{
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= n) return;
+    const int lane = (int)(e & 63);
+    const int64_t st = e >> 6, q = 16 * (st / ns) + (lane & 15);
+    const int j = 4 * (int)(st % ns) + (lane >> 4);
+    Xt[e] = (q < G && j < N) ? S64[q * N + j] - off[j] : 0.0;
+}
+
+// Candidates of one row: cand[row][stride] holds the kernel's n_chunks values
+// and +inf past them (the kernels of one round take different chunk counts).
+__device__ __forceinline__ void fixed_candidate(double *__restrict__ cand_v,
+                                                int64_t *__restrict__ cand_q, int64_t r, int stride,
+                                                int chunk, int n_chunks, double v, int64_t q)
+{
+    cand_v[r * stride + chunk] = v;
+    cand_q[r * stride + chunk] = q;
+    if (chunk + 1 == n_chunks)
+        for (int c = n_chunks; c < stride; ++c) {
+            cand_v[r * stride + c] = __builtin_inf();
+            cand_q[r * stride + c] = INT64_MAX;
+        }
+}
+
+// Running minimum of one tile of at most 16 NU universes of one matrix against
+// the grid points of one chunk; outputs as k_fixed_min.  W_m stays in
+// registers for NU = 1; for NU = 2 the universes take them and W_m sits in LDS.
+template <int NS, int NU>
+__global__ __launch_bounds__(kFxThreads) __attribute__((amdgpu_waves_per_eu(2))) void
+k_fixed_small(const FxTileDesc *__restrict__ tiles, int64_t n_tiles,
+              const double *__restrict__ W64, const double *__restrict__ Xt,
+              const double *__restrict__ Y, const double *__restrict__ a,
+              const int64_t *__restrict__ p_of_row, int N, int64_t G, int64_t q_per_chunk,
+              int n_chunks, int stride, double *__restrict__ cand_v,
+              int64_t *__restrict__ cand_q, double *__restrict__ cp)
+{
+    constexpr int NP = 4 * NS, NC = (NP + 15) / 16;
+    // steps of component block c: up to the diagonal
+    constexpr auto steps = [](int c) { return 4 * c + 4 < NS ? 4 * c + 4 : NS; };
+    constexpr bool kLds = NU > 1;
+    __shared__ double wl[kLds ? NC * NS * 64 : 1];
+    __shared__ double red_v[4][16 * NU];
+    __shared__ int32_t red_q[4][16 * NU];
+    const int64_t tile = blockIdx.x % n_tiles;
+    const int chunk = (int)(blockIdx.x / n_tiles);
+    const FxTileDesc td = tiles[tile];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int grp = lane >> 4, col = lane & 15;
+    const int64_t qb = (int64_t)chunk * q_per_chunk;
+    const int64_t qe = (qb + q_per_chunk < G) ? qb + q_per_chunk : G;
+
+    // A operands: W_m rows 16 c + col at bins 4 s + grp, and y of universe
+    // 16 u + col at the same bins
+    const double *Wm = W64 + (int64_t)td.slot * ((int64_t)N * (N + 1) / 2);
+    double wf[kLds ? 1 : NC][NS], yf[NU][NS];
+    static_for<0, NC>([&](auto cc) {
+        constexpr int c = decltype(cc)::value;
+        const int i = 16 * c + col;
+        static_for<0, steps(c)>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            const int j = 4 * s + grp;
+            if constexpr (kLds) {
+                if (wave == (c + s) % 4)
+                    wl[(c * NS + s) * 64 + lane] =
+                        (i < N && j <= i) ? Wm[(int64_t)i * (i + 1) / 2 + j] : 0.0;
+            } else {
+                wf[c][s] = (i < N && j <= i) ? Wm[(int64_t)i * (i + 1) / 2 + j] : 0.0;
+            }
+        });
+    });
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            yf[u][s] = 16 * u + col < td.n ? Y[(td.r0 + 16 * u + col) * NP + 4 * s + grp] : 0.0;
+    // the lane's universes in the output layout: rows 16 u + grp + 4 j
+    double av[NU][4], best[NU][4];
+    int32_t pv[NU][4], bq[NU][4];
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = 16 * u + grp + 4 * j;
+            av[u][j] = k < td.n ? a[td.r0 + k] : 0.0;
+            pv[u][j] = k < td.n ? (int32_t)p_of_row[td.r0 + k] : -1;
+            best[u][j] = __builtin_inf();
+            bq[u][j] = INT32_MAX;
+        }
+    if constexpr (kLds) __syncthreads();
+    const int t1 = (int)((qe - qb + 15) / 16);  // 16-point tiles of the chunk
+    const double *xt = Xt + (qb / 16) * (64 * NS) + lane;
+    double x[NS];
+    const auto fetch = [&](int t) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) x[s] = xt[(int64_t)t * (64 * NS) + 64 * s];
+    };
+    if (wave < t1) fetch(wave);
+    for (int t = wave; t < t1; t += 4) {
+        v4d acc[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[c] = v4d{0.0, 0.0, 0.0, 0.0};
+        static_for<0, NS>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            static_for<0, NC>([&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                if constexpr (s < steps(c)) {
+                    double w;
+                    if constexpr (kLds)
+                        w = wl[(c * NS + s) * 64 + lane];
+                    else
+                        w = wf[c][s];
+                    acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(w, x[s], acc[c], 0, 0, 0);
+                }
+            });
+        });
+        if (t + 4 < t1) fetch(t + 4);
+        // t^T: lane holds component 16 c + grp + 4 r of grid point col, the B
+        // operand of step 4 c + r
+        v4d z[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) z[u] = v4d{0.0, 0.0, 0.0, 0.0};
+        static_for<0, NS>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+                z[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(yf[u][s], acc[s / 4][s % 4], z[u], 0, 0, 0);
+        });
+        // b_q, summed as in k_fixed_t: over c, then over i % 16 = grp + 4 r pairwise
+        double sq[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            sq[r] = 0.0;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) sq[r] = fma(acc[c][r], acc[c][r], sq[r]);
+            sq[r] += __shfl_xor(sq[r], 16);
+            sq[r] += __shfl_xor(sq[r], 32);
+        }
+        const double b = (sq[0] + sq[1]) + (sq[2] + sq[3]);
+        const int32_t q = (int32_t)qb + 16 * t + col;
+        if (q < qe) {
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double v = (av[u][j] + b) - 2.0 * z[u][j];
+                    if (q == pv[u][j]) cp[td.r0 + 16 * u + grp + 4 * j] = v;
+                    if (v < best[u][j]) {
+                        best[u][j] = v;
+                        bq[u][j] = q;
+                    }
+                }
+        }
+    }
+    // minimum over the 16 grid points of each wave's steps, then over waves;
+    // ties go to the lower q
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            double v = best[u][j];
+            int32_t q = bq[u][j];
+#pragma unroll
+            for (int sh = 1; sh <= 8; sh <<= 1) {
+                const double ov = __shfl_xor(v, sh);
+                const int32_t oq = __shfl_xor(q, sh);
+                if (ov < v || (ov == v && oq < q)) {
+                    v = ov;
+                    q = oq;
+                }
+            }
+            if (col == 0) {
+                red_v[wave][16 * u + grp + 4 * j] = v;
+                red_q[wave][16 * u + grp + 4 * j] = q;
+            }
+        }
+    __syncthreads();
+    if (tid < td.n) {
+        double v = red_v[0][tid];
+        int32_t q = red_q[0][tid];
+        for (int w = 1; w < 4; ++w) {
+            const double ov = red_v[w][tid];
+            const int32_t oq = red_q[w][tid];
+            if (ov < v || (ov == v && oq < q)) {
+                v = ov;
+                q = oq;
+            }
+        }
+        fixed_candidate(cand_v, cand_q, td.r0 + tid, stride, chunk, n_chunks, v, q);
+    }
+}
+
 // Running minimum of one (tile, grid chunk): candidates cand_v/cand_q
-// [row][n_chunks], chi2 at the true point into cp[row] (exactly one block
+// [row][stride], chi2 at the true point into cp[row] (exactly one block
 // meets q == p for each row).
 template <int NS>
 __global__ __launch_bounds__(kFxThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_fixed_min(
     const FxTileDesc *__restrict__ tiles, int64_t n_tiles, const double *__restrict__ Y,
     const double *__restrict__ a, const int64_t *__restrict__ p_of_row,
     const double *__restrict__ T, const double *__restrict__ b, int64_t b_stride, int64_t G,
-    int64_t q_per_chunk, int n_chunks, double *__restrict__ cand_v, int64_t *__restrict__ cand_q,
-    double *__restrict__ cp)
+    int64_t q_per_chunk, int n_chunks, int stride, double *__restrict__ cand_v,
+    int64_t *__restrict__ cand_q, double *__restrict__ cp)
 {
     constexpr int NP = 4 * NS;             // padded bins
     constexpr int TU = kFxTile * NP / 2;   // 16-byte units of a t tile (rows contiguous)
@@ -307,9 +521,7 @@ __global__ __launch_bounds__(kFxThreads) __attribute__((amdgpu_waves_per_eu(2)))
                 q = oq;
             }
         }
-        const int64_t r = td.r0 + tid;
-        cand_v[r * n_chunks + chunk] = v;
-        cand_q[r * n_chunks + chunk] = q;
+        fixed_candidate(cand_v, cand_q, td.r0 + tid, stride, chunk, n_chunks, v, q);
     }
 }
 
@@ -363,33 +575,75 @@ struct Buf {
     template <class T> T *as() const { return reinterpret_cast<T *>(p); }
 };
 
+// One kernel's tiles of a round and their grid chunks (whole steps of kFxTile
+// points).
+struct FxLaunch {
+    const FxTileDesc *tiles = nullptr;
+    int64_t n_tiles = 0, q_per_chunk = 0;
+    int n_chunks = 0;
+
+    void chunks(int64_t G, int slots)
+    {
+        const int64_t steps = (G + kFxTile - 1) / kFxTile;
+        const ScanGeometry sg = scan_geometry(n_tiles, n_tiles, steps, slots, steps);
+        q_per_chunk = sg.q_per_chunk * kFxTile;
+        n_chunks = (int)sg.n_qchunks;
+    }
+};
+
+// Device arrays of a round's rows.
+struct FxRows {
+    const double *Y, *a;
+    const int64_t *p;
+    int stride;
+    double *cand_v;
+    int64_t *cand_q;
+    double *cp;
+};
+
 template <int NS>
-hipError_t launch_fixed_min_ns(const FxTileDesc *tiles, int64_t n_tiles, const double *Y,
-                               const double *a, const int64_t *p_of_row, const double *T,
-                               const double *b, int64_t b_stride, int64_t G, int64_t q_per_chunk,
-                               int n_chunks, double *cand_v, int64_t *cand_q, double *cp,
-                               hipStream_t st)
+hipError_t launch_fixed_min_ns(const fc_grid *g, const FxLaunch &l, const FxRows &r,
+                               const double *T, const double *b, int64_t b_stride, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_fixed_min<NS>), dim3((unsigned)(n_tiles * n_chunks)), dim3(kFxThreads),
-                       0, st, tiles, n_tiles, Y, a, p_of_row, T, b, b_stride, G, q_per_chunk,
-                       n_chunks, cand_v, cand_q, cp);
+    hipLaunchKernelGGL((k_fixed_min<NS>), dim3((unsigned)(l.n_tiles * l.n_chunks)),
+                       dim3(kFxThreads), 0, st, l.tiles, l.n_tiles, r.Y, r.a, r.p, T, b, b_stride,
+                       g->G, l.q_per_chunk, l.n_chunks, r.stride, r.cand_v, r.cand_q, r.cp);
     return hipGetLastError();
 }
 
-hipError_t launch_fixed_min(int ns, const FxTileDesc *tiles, int64_t n_tiles, const double *Y,
-                            const double *a, const int64_t *p_of_row, const double *T,
-                            const double *b, int64_t b_stride, int64_t G, int64_t q_per_chunk,
-                            int n_chunks, double *cand_v, int64_t *cand_q, double *cp,
-                            hipStream_t st)
+template <int NS, int NU>
+hipError_t launch_fixed_small_ns(const fc_grid *g, const FxLaunch &l, const FxRows &r,
+                                 const double *Xt, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_fixed_small<NS, NU>), dim3((unsigned)(l.n_tiles * l.n_chunks)),
+                       dim3(kFxThreads), 0, st, l.tiles, l.n_tiles, g->W64, Xt, r.Y, r.a, r.p, g->N,
+                       g->G, l.q_per_chunk, l.n_chunks, r.stride, r.cand_v, r.cand_q, r.cp);
+    return hipGetLastError();
+}
+
+#define FC_EACH_NS(X)                                                                     \
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+
+hipError_t launch_fixed_min(int ns, const fc_grid *g, const FxLaunch &l, const FxRows &r,
+                            const double *T, const double *b, int64_t b_stride, hipStream_t st)
 {
     switch (ns) {
-#define FC_CASE(n)                                                                                \
-    case n:                                                                                       \
-        return launch_fixed_min_ns<n>(tiles, n_tiles, Y, a, p_of_row, T, b, b_stride, G,          \
-                                      q_per_chunk, n_chunks, cand_v, cand_q, cp, st);
-        FC_CASE(1) FC_CASE(2) FC_CASE(3) FC_CASE(4) FC_CASE(5) FC_CASE(6) FC_CASE(7) FC_CASE(8)
-        FC_CASE(9) FC_CASE(10) FC_CASE(11) FC_CASE(12) FC_CASE(13) FC_CASE(14) FC_CASE(15)
-        FC_CASE(16)
+#define FC_CASE(n) case n: return launch_fixed_min_ns<n>(g, l, r, T, b, b_stride, st);
+        FC_EACH_NS(FC_CASE)
+#undef FC_CASE
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_fixed_small(int ns, int nu, const fc_grid *g, const FxLaunch &l, const FxRows &r,
+                              const double *Xt, hipStream_t st)
+{
+    switch (ns) {
+#define FC_CASE(n)                                                       \
+    case n:                                                              \
+        return nu == 1 ? launch_fixed_small_ns<n, 1>(g, l, r, Xt, st)    \
+                       : launch_fixed_small_ns<n, 2>(g, l, r, Xt, st);
+        FC_EACH_NS(FC_CASE)
 #undef FC_CASE
     default: return hipErrorInvalidValue;
     }
@@ -411,9 +665,7 @@ hipError_t launch_fixed_t(int ns, const fc_grid *g, const int64_t *m_of_slot, in
     switch (ns) {
 #define FC_CASE(n) \
     case n: return launch_fixed_t_ns<n>(g, m_of_slot, n_slots, b_stride, T, b, st);
-        FC_CASE(1) FC_CASE(2) FC_CASE(3) FC_CASE(4) FC_CASE(5) FC_CASE(6) FC_CASE(7) FC_CASE(8)
-        FC_CASE(9) FC_CASE(10) FC_CASE(11) FC_CASE(12) FC_CASE(13) FC_CASE(14) FC_CASE(15)
-        FC_CASE(16)
+        FC_EACH_NS(FC_CASE)
 #undef FC_CASE
     default: return hipErrorInvalidValue;
     }
@@ -431,70 +683,95 @@ static hipError_t fixed_round(const fc_grid *g, int64_t R, const std::vector<int
 {
     const int N = g->N, ns = (N + 3) / 4, np = 4 * ns;
     const int64_t G = g->G;
-    // groups: runs of equal m; matrix slots batched so that t fits a budget
+    // groups: runs of equal m; the t tables of the larger groups in slots,
+    // batched so that they fit a budget
     const int64_t b_stride = G + (G & 1) + 2;  // even (16-byte rows) plus a pair of slack
     const size_t t_bytes_per_slot = sizeof(double) * ((size_t)G * np + b_stride);
     const size_t budget = size_t(4) << 30;
     const int64_t slots_max = std::max<int64_t>(1, (int64_t)(budget / t_bytes_per_slot));
     Buf &dOrder = bufs[0], &dM = bufs[1], &dP = bufs[2], &dY = bufs[3], &dA = bufs[4],
         &dT = bufs[5], &dB = bufs[6], &dSlotM = bufs[7], &dTiles = bufs[8], &dCv = bufs[9],
-        &dCq = bufs[10], &dCp = bufs[11];
+        &dCq = bufs[10], &dCp = bufs[11], &dX = bufs[12];
     hipError_t e;
     int64_t r_begin = 0;
     while (r_begin < R) {
-        // rows r_begin .. r_end cover at most slots_max distinct m
+        // rows r_begin .. r_end cover at most slots_max groups with a t table
         std::vector<int64_t> slot_m;
-        std::vector<FxTileDesc> tiles;
+        // tiles of k_fixed_min, and of k_fixed_small with one and two blocks of 16
+        std::vector<FxTileDesc> tiles, small[2];
         int64_t r = r_begin;
-        while (r < R && (int64_t)slot_m.size() < slots_max) {
+        while (r < R) {
             const int64_t m = h_m[r];
             int64_t r2 = r;
             while (r2 < R && h_m[r2] == m) ++r2;
-            const int32_t slot = (int32_t)slot_m.size();
-            slot_m.push_back(m);
-            for (int64_t t0 = r; t0 < r2; t0 += kFxTile) {
-                FxTileDesc td;
+            const bool table = r2 - r > kFxSmall;
+            if (table && (int64_t)slot_m.size() == slots_max) break;
+            FxTileDesc td;
+            td.slot = table ? (int32_t)slot_m.size() : (int32_t)m;
+            if (table) slot_m.push_back(m);
+            for (int64_t t0 = r; t0 < r2; t0 += td.n) {
                 td.r0 = t0 - r_begin;
-                td.n = (int32_t)std::min<int64_t>(kFxTile, r2 - t0);
-                td.slot = slot;
-                tiles.push_back(td);
+                td.n = (int32_t)std::min<int64_t>(table ? kFxTile : 32, r2 - t0);
+                (table ? tiles : small[td.n > 16]).push_back(td);
             }
             r = r2;
         }
         const int64_t r_end = r, nr = r_end - r_begin, n_slots = (int64_t)slot_m.size();
-        const int64_t n_tiles = (int64_t)tiles.size();
-        // grid chunks: enough blocks to fill the chip, chunks of whole tiles
-        static const int slots_res =  // queried once (thread-safe)
+        static const int slots_res =  // queried once (thread-safe); all three: two blocks a CU
             resident_slots(reinterpret_cast<const void *>(&k_fixed_min<15>), kFxThreads);
-        int n_chunks = (int)std::max<int64_t>(1, (4 * (int64_t)slots_res + n_tiles - 1) / n_tiles);
-        const int64_t max_chunks = std::max<int64_t>(1, (G + kFxTile - 1) / kFxTile);
-        n_chunks = (int)std::min<int64_t>(n_chunks, max_chunks);
-        int64_t qpc = (G + n_chunks - 1) / n_chunks;
-        qpc = ((qpc + kFxTile - 1) / kFxTile) * kFxTile;
-        n_chunks = (int)((G + qpc - 1) / qpc);
+        FxLaunch big, sm[2];
+        big.n_tiles = (int64_t)tiles.size();
+        for (int k = 0; k < 2; ++k) {
+            sm[k].n_tiles = (int64_t)small[k].size();
+            tiles.insert(tiles.end(), small[k].begin(), small[k].end());
+        }
+        const int64_t all = (int64_t)tiles.size();
+        FxRows rows;
+        rows.stride = 1;
+        for (FxLaunch *l : {&big, &sm[0], &sm[1]})
+            if (l->n_tiles) {
+                l->chunks(G, slots_res);
+                rows.stride = std::max(rows.stride, l->n_chunks);
+            }
+        const int64_t nx = (G + 15) / 16 * 64 * ns;  // elements of X
 
         if ((e = dOrder.need(sizeof(int64_t) * nr)) != hipSuccess ||
             (e = dM.need(sizeof(int64_t) * nr)) != hipSuccess ||
             (e = dP.need(sizeof(int64_t) * nr)) != hipSuccess ||
             (e = dY.need(sizeof(double) * nr * np)) != hipSuccess ||
             (e = dA.need(sizeof(double) * nr)) != hipSuccess ||
-            (e = dT.need(sizeof(double) * (size_t)n_slots * G * np)) != hipSuccess ||
-            (e = dB.need(sizeof(double) * (size_t)n_slots * b_stride)) != hipSuccess ||
-            (e = dSlotM.need(sizeof(int64_t) * n_slots)) != hipSuccess ||
-            (e = dTiles.need(sizeof(FxTileDesc) * n_tiles)) != hipSuccess ||
-            (e = dCv.need(sizeof(double) * nr * n_chunks)) != hipSuccess ||
-            (e = dCq.need(sizeof(int64_t) * nr * n_chunks)) != hipSuccess ||
+            (n_slots && (e = dT.need(sizeof(double) * (size_t)n_slots * G * np)) != hipSuccess) ||
+            (n_slots && (e = dB.need(sizeof(double) * (size_t)n_slots * b_stride)) != hipSuccess) ||
+            (n_slots && (e = dSlotM.need(sizeof(int64_t) * n_slots)) != hipSuccess) ||
+            (e = dTiles.need(sizeof(FxTileDesc) * all)) != hipSuccess ||
+            (e = dCv.need(sizeof(double) * nr * rows.stride)) != hipSuccess ||
+            (e = dCq.need(sizeof(int64_t) * nr * rows.stride)) != hipSuccess ||
             (e = dCp.need(sizeof(double) * nr)) != hipSuccess)
             return e;
+        big.tiles = dTiles.as<FxTileDesc>();
+        sm[0].tiles = big.tiles + big.n_tiles;
+        sm[1].tiles = sm[0].tiles + sm[0].n_tiles;
+        rows.Y = dY.as<double>();
+        rows.a = dA.as<double>();
+        rows.p = dP.as<int64_t>();
+        rows.cand_v = dCv.as<double>();
+        rows.cand_q = dCq.as<int64_t>();
+        rows.cp = dCp.as<double>();
+        if (sm[0].n_tiles + sm[1].n_tiles && !dX.p) {  // once per call
+            if ((e = dX.need(sizeof(double) * (size_t)nx)) != hipSuccess) return e;
+            hipLaunchKernelGGL(k_fixed_x, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st,
+                               g->S64, g->off, N, ns, G, nx, dX.as<double>());
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
         if ((e = hipMemcpyAsync(dOrder.p, h_order.data() + r_begin, sizeof(int64_t) * nr,
                                 hipMemcpyHostToDevice, st)) != hipSuccess ||
             (e = hipMemcpyAsync(dM.p, h_m.data() + r_begin, sizeof(int64_t) * nr,
                                 hipMemcpyHostToDevice, st)) != hipSuccess ||
             (e = hipMemcpyAsync(dP.p, h_p.data() + r_begin, sizeof(int64_t) * nr,
                                 hipMemcpyHostToDevice, st)) != hipSuccess ||
-            (e = hipMemcpyAsync(dSlotM.p, slot_m.data(), sizeof(int64_t) * n_slots,
-                                hipMemcpyHostToDevice, st)) != hipSuccess ||
-            (e = hipMemcpyAsync(dTiles.p, tiles.data(), sizeof(FxTileDesc) * n_tiles,
+            (n_slots && (e = hipMemcpyAsync(dSlotM.p, slot_m.data(), sizeof(int64_t) * n_slots,
+                                            hipMemcpyHostToDevice, st)) != hipSuccess) ||
+            (e = hipMemcpyAsync(dTiles.p, tiles.data(), sizeof(FxTileDesc) * all,
                                 hipMemcpyHostToDevice, st)) != hipSuccess)
             return e;
         // chi2 at the true point is always met (p is a grid point); NaN until then
@@ -502,16 +779,18 @@ static hipError_t fixed_round(const fc_grid *g, int64_t R, const std::vector<int
                            g->off, dOrder.as<int64_t>(), dM.as<int64_t>(), N, np, nr,
                            dY.as<double>(), dA.as<double>());
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = launch_fixed_t(ns, g, dSlotM.as<int64_t>(), n_slots, b_stride, dT.as<double>(),
-                                dB.as<double>(), st)) != hipSuccess)
+        if (big.n_tiles &&
+            ((e = launch_fixed_t(ns, g, dSlotM.as<int64_t>(), n_slots, b_stride, dT.as<double>(),
+                                 dB.as<double>(), st)) != hipSuccess ||
+             (e = launch_fixed_min(ns, g, big, rows, dT.as<double>(), dB.as<double>(), b_stride,
+                                   st)) != hipSuccess))
             return e;
-        if ((e = launch_fixed_min(ns, dTiles.as<FxTileDesc>(), n_tiles, dY.as<double>(),
-                                  dA.as<double>(), dP.as<int64_t>(), dT.as<double>(),
-                                  dB.as<double>(), b_stride, G, qpc, n_chunks, dCv.as<double>(),
-                                  dCq.as<int64_t>(), dCp.as<double>(), st)) != hipSuccess)
-            return e;
+        for (int k = 0; k < 2; ++k)
+            if (sm[k].n_tiles && (e = launch_fixed_small(ns, k + 1, g, sm[k], rows,
+                                                         dX.as<double>(), st)) != hipSuccess)
+                return e;
         hipLaunchKernelGGL(k_fixed_finish, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, st,
-                           nr, n_chunks, dCv.as<double>(), dCq.as<int64_t>(), dCp.as<double>(),
+                           nr, rows.stride, dCv.as<double>(), dCq.as<int64_t>(), dCp.as<double>(),
                            dOrder.as<int64_t>(), dP.as<int64_t>(), dchi2, chi2_min, argmin,
                            chi2_p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -536,7 +815,7 @@ hipError_t fixed_run(const fc_grid *g, int64_t K, const double *d, const int64_t
         return e;
     for (int64_t k = 0; k < K; ++k) m[k] = p[k];
     std::vector<char> active(K, 1);
-    Buf bufs[12];
+    Buf bufs[13];
     std::vector<int64_t> order, hm, hp, cnt;
     for (int round = 0;; ++round) {
         // counting sort of the active universes by m

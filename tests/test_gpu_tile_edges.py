@@ -9,7 +9,8 @@ import pytest
 
 import oracle
 import parity
-from test_gpu_scan import FORM, fc, run_points, run_scan  # noqa: F401  (fc: fixture)
+from test_gpu_fixed import run_fixed
+from test_gpu_scan import FORM, fc, run_scan  # noqa: F401  (fc: fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +44,25 @@ def test_fp64_tiles_and_groups(fc, N, K, G):  # noqa: F811
     fc.fc_build_covariance(g, F, forms=FORM["fp64"])
     ref = oracle.scan(S, F, d, p)
     check(run_scan(fc, g, FORM["fp64"], d, p), ref, S, F, d, p, parity.TOL["fp64"])
+
+
+# groups of one matrix at the borders of the tiles (16, 32) and of the rule
+# between on-the-fly and tabulated points (256), several groups a call
+@pytest.mark.parametrize("N", [1, 4, 5, 16, 17, 32, 33, 48, 57, 64])
+@pytest.mark.parametrize("iters", [0, 5])
+def test_fixed_matrix_groups(fc, N, iters):  # noqa: F811
+    sizes = (1, 16, 17, 33, 256, 257, 2)
+    G = 77  # not a multiple of 16 or 64
+    S, F, _, _ = small_problem(N, G, 1, 3)
+    rng = np.random.default_rng([N, iters])
+    p = np.repeat(np.sort(rng.choice(G, len(sizes), replace=False)), sizes)
+    p = p[rng.permutation(p.size)]
+    d = S[p] + rng.standard_normal((p.size, N)) * np.sqrt(S[p])
+    g = fc.fc_build_grid([np.arange(G, dtype=float)], S)
+    fc.fc_build_covariance(g, F, forms=FORM["fp64"])
+    dev = run_fixed(fc, g, d, p, iters)
+    ref = oracle.scan_fixed_m(S, F, d, p, iters)
+    scale = np.maximum(1.0, ref["chi2_p"])
+    assert np.all(np.abs(dev["dchi2"] - ref["dchi2"]) <= parity.TOL["fp64"] * scale)
+    for k in ("argmin", "m_final", "iters"):
+        assert np.array_equal(dev[k], ref[k]), k
