@@ -22,10 +22,22 @@
 // cos(2 pi u1) from words 0 and 1 of the bin's normal block.  A mean that is
 // negative, NaN or infinite gives count -1 and d = NaN.
 //
-// One wave per universe, lane i = bin i; L_F sits in LDS.  The arithmetic is
-// FP64 without contraction, in the order written, so the counts are the same
-// integers on any IEEE machine that evaluates exp/log/lgamma to within an ulp
-// (a decision flips only if a uniform lands within rounding of a boundary).
+// A block takes kGenRows universes at a time, one thread per (universe, bin).
+// Most Poisson draws end at the first attempt's squeeze; with a lane per bin of
+// one universe, some lane of every wave needed the exact test (two logarithms
+// and lgamma) and the whole wave waited through it up to four times.  The draws
+// that the squeeze does not settle therefore go to a list in LDS and are drawn
+// afterwards with full waves.  The constants of the squeeze depend on (p, bin)
+// alone and are tabulated per block while consecutive universes share p; L_F
+// sits in LDS by columns (consecutive bins, consecutive addresses).  Bound:
+// FP64 and 64-bit integer vector arithmetic (two Philox blocks of 20 64 x 64
+// products each).  16 x 10 000 universes, N = 57: 1.12 ms with one wave per
+// universe, 0.47 ms so.
+//
+// The arithmetic is FP64 without contraction, in the order written, so the
+// counts are the same integers on any IEEE machine that evaluates
+// exp/log/lgamma to within an ulp (a decision flips only if a uniform lands
+// within rounding of a boundary).
 #include "fc_internal.h"
 
 namespace fcx {
@@ -64,6 +76,32 @@ __device__ __forceinline__ double unit_open(uint64_t w)
     return ((double)(w >> 11) + 0.5) * 0x1.0p-53;
 }
 
+// PTRS constants of a mean (functions of sqrt(lambda) only)
+struct Ptrs {
+    double A, B, vr;
+};
+__device__ __forceinline__ Ptrs ptrs_constants(double lam)
+{
+    Ptrs c;
+    c.B = 0.931 + 2.53 * sqrt(lam);
+    c.A = -0.059 + 0.02483 * c.B;
+    c.vr = 0.9277 - 3.6224 / (c.B - 2.0);
+    return c;
+}
+// PTRS candidate of the words (wu, wv): its count kf, with us and V
+__device__ __forceinline__ double ptrs_candidate(const Ptrs &c, double lam, uint64_t wu,
+                                                 uint64_t wv, double &us, double &V)
+{
+    const double U = unit_open(wu) - 0.5;
+    V = unit_open(wv);
+    us = 0.5 - fabs(U);
+    return floor((2.0 * c.A / us + c.B) * U + lam + 0.43);
+}
+__device__ __forceinline__ bool ptrs_squeeze(const Ptrs &c, double us, double V)
+{
+    return us >= 0.07 && V <= c.vr;
+}
+
 // Poisson count for bin i of universe j at point p (-1: no valid mean).
 __device__ int64_t poisson_draw(double lam, uint64_t seed, int64_t p, int64_t j, int i)
 {
@@ -84,22 +122,17 @@ __device__ int64_t poisson_draw(double lam, uint64_t seed, int64_t p, int64_t j,
         }
         return k;
     }
-    // PTRS constants (functions of sqrt(lambda) only)
-    const double sq = sqrt(lam), ll = log(lam);
-    const double B = 0.931 + 2.53 * sq;
-    const double A = -0.059 + 0.02483 * B;
-    const double ia = 1.1239 + 1.1328 / (B - 3.4);
-    const double vr = 0.9277 - 3.6224 / (B - 2.0);
+    const Ptrs c = ptrs_constants(lam);
+    const double ll = log(lam);
+    const double ia = 1.1239 + 1.1328 / (c.B - 3.4);
     for (uint32_t t = 0; t < 512; ++t) {
         if ((t & 1u) == 0u) stream_block(seed, p, j, i, 0, t >> 1, w);
         const int h = 2 * (int)(t & 1u);
-        const double U = unit_open(w[h]) - 0.5;
-        const double V = unit_open(w[h + 1]);
-        const double us = 0.5 - fabs(U);
-        const double kf = floor((2.0 * A / us + B) * U + lam + 0.43);
-        if (us >= 0.07 && V <= vr) return (int64_t)kf;         // squeeze: accept
+        double us, V;
+        const double kf = ptrs_candidate(c, lam, w[h], w[h + 1], us, V);
+        if (ptrs_squeeze(c, us, V)) return (int64_t)kf;        // accept
         if (kf < 0.0 || (us < 0.013 && V > us)) continue;      // outside the hat
-        const double lhs = log(V * ia / (A / (us * us) + B));
+        const double lhs = log(V * ia / (c.A / (us * us) + c.B));
         const double rhs = -lam + kf * ll - lgamma(kf + 1.0);
         if (lhs <= rhs) return (int64_t)kf;
     }
@@ -161,41 +194,85 @@ __device__ __forceinline__ int64_t segment_of(const int64_t *__restrict__ seg_of
     return lo;
 }
 
-__global__ __launch_bounds__(256) void k_gen_universes(
+constexpr int kGenRows = 16;  // universes of a block at most
+
+// One tile of at most kGenRows universes a block (a loop over tiles lets the
+// compiler keep the library functions' constants in registers across it: 555
+// us at three waves per SIMD with spills, against 466).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gen_universes(
     const double *__restrict__ S64, const double *__restrict__ LF, int N, int64_t G,
     int64_t n_pts, const int64_t *__restrict__ p, const int64_t *__restrict__ seg_off,
-    const int64_t *__restrict__ u_first, uint64_t seed, int64_t K, double *__restrict__ d,
-    int64_t *__restrict__ p_idx, int32_t *__restrict__ counts)
+    const int64_t *__restrict__ u_first, uint64_t seed, int64_t row0, int64_t K, int tile_rows,
+    double *__restrict__ d, int64_t *__restrict__ p_idx, int32_t *__restrict__ counts)
 {
-    __shared__ double lf[kMaxBins * kMaxBins];
-    for (int e = threadIdx.x; e < N * N; e += blockDim.x) lf[e] = LF[e];
-    __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t r = wave; r < K; r += n_waves) {
-        const int64_t k = segment_of(seg_off, n_pts, r);
+    __shared__ double lft[kMaxBins * kMaxBins];  // L_F by columns: lft[l N + i]
+    __shared__ double gs[kGenRows][kMaxBins];    // normals
+    __shared__ int64_t ns[kGenRows][kMaxBins];   // counts
+    __shared__ Ptrs cs[kMaxBins];                // squeeze constants of point p_cs
+    __shared__ double lam_s[kMaxBins];           // its means
+    __shared__ int64_t pk_s[kGenRows], j_s[kGenRows];
+    __shared__ uint16_t slow[kGenRows * kMaxBins];  // draws the squeeze left open
+    __shared__ int n_slow;
+    const int tid = threadIdx.x;
+    for (int e = tid; e < N * N; e += 256) lft[(e % N) * N + e / N] = LF[e];
+    const int64_t r0 = row0 + (int64_t)blockIdx.x * tile_rows;
+    if (r0 >= K) return;
+    const int rows = (int)(K - r0 < tile_rows ? K - r0 : tile_rows);
+    if (tid < rows) {
+        const int64_t k = segment_of(seg_off, n_pts, r0 + tid);
         const int64_t pk = p[k];
-        const int64_t j = (u_first ? u_first[k] : 0) + (r - seg_off[k]);
-        const bool valid = pk >= 0 && pk < G;
-        double g = 0.0, lam = 0.0;
+        pk_s[tid] = (pk >= 0 && pk < G) ? pk : -1;
+        j_s[tid] = (u_first ? u_first[k] : 0) + (r0 + tid - seg_off[k]);
+        if (p_idx) p_idx[r0 + tid] = pk_s[tid];
+    }
+    if (tid == 0) n_slow = 0;
+    __syncthreads();
+    const int64_t p_cs = pk_s[0];  // the point whose constants are tabulated
+    if (tid < N && p_cs >= 0) {
+        lam_s[tid] = S64[p_cs * N + tid];
+        cs[tid] = ptrs_constants(lam_s[tid]);
+    }
+    __syncthreads();
+    // normals, and the counts that the first attempt's squeeze settles
+    for (int e = tid; e < rows * N; e += 256) {
+        const int u = e / N, i = e - u * N;
+        const int64_t pk = pk_s[u], j = j_s[u];
+        double g = 0.0;
         int64_t n = -1;
-        if (valid && lane < N) {
-            lam = S64[pk * N + lane];
-            g = normal_draw(seed, pk, j, lane);
-            n = poisson_draw(lam, seed, pk, j, lane);
+        if (pk >= 0) {
+            g = normal_draw(seed, pk, j, i);
+            bool open = true;
+            if (pk == p_cs && lam_s[i] >= 10.0 && !__builtin_isinf(lam_s[i])) {
+                uint64_t w[4];
+                stream_block(seed, pk, j, i, 0, 0, w);
+                double us, V;
+                const double kf = ptrs_candidate(cs[i], lam_s[i], w[0], w[1], us, V);
+                if (ptrs_squeeze(cs[i], us, V)) {
+                    n = (int64_t)kf;
+                    open = false;
+                }
+            }
+            if (open) slow[atomicAdd(&n_slow, 1)] = (uint16_t)(u * kMaxBins + i);
         }
-        // z_i = sum_{l <= i} L_F[i][l] g_l, increasing l
+        gs[u][i] = g;
+        ns[u][i] = n;
+    }
+    __syncthreads();
+    for (int e = tid; e < n_slow; e += 256) {
+        const int u = slow[e] / kMaxBins, i = slow[e] % kMaxBins;
+        ns[u][i] = poisson_draw(S64[pk_s[u] * N + i], seed, pk_s[u], j_s[u], i);
+    }
+    __syncthreads();
+    // z_i = sum_{l <= i} L_F[i][l] g_l, increasing l
+    for (int e = tid; e < rows * N; e += 256) {
+        const int u = e / N, i = e - u * N;
         double z = 0.0;
-        for (int l = 0; l < N; ++l) {
-            const double gl = __shfl(g, l);
-            if (l <= lane) z = z + lf[(lane < N ? lane : 0) * N + l] * gl;
-        }
-        if (lane < N) {
-            d[r * N + lane] = (n < 0) ? __builtin_nan("") : (double)n + lam * z;
-            if (counts) counts[r * N + lane] = (int32_t)n;
-        }
-        if (lane == 0 && p_idx) p_idx[r] = valid ? pk : -1;
+#pragma unroll 8
+        for (int l = 0; l < N; ++l) z = z + lft[l * N + i] * gs[u][l];  // L_F is 0 past i
+        const int64_t pk = pk_s[u], n = ns[u][i];
+        const double lam = pk < 0 ? 0.0 : (pk == p_cs ? lam_s[i] : S64[pk * N + i]);
+        d[(r0 + u) * N + i] = (n < 0) ? __builtin_nan("") : (double)n + lam * z;
+        if (counts) counts[(r0 + u) * N + i] = (int32_t)n;
     }
 }
 
@@ -210,11 +287,18 @@ hipError_t launch_gen_universes(const fc_grid *g, int64_t n_pts, const int64_t *
                                 int64_t K, double *d, int64_t *p_idx, int32_t *counts,
                                 hipStream_t st)
 {
-    const int64_t rows_per_block = 4;
-    int64_t blocks = (K + rows_per_block - 1) / rows_per_block;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(k_gen_universes, dim3((unsigned)blocks), dim3(256), 0, st, g->S64, g->LF64,
-                       g->N, g->G, n_pts, p, seg_off, u_first, seed, K, d, p_idx, counts);
+    // few universes: smaller tiles, down to one bin a thread, on more CUs
+    static const int slots =  // queried once (thread-safe)
+        resident_slots(reinterpret_cast<const void *>(&k_gen_universes), 256);
+    const int64_t share = K / slots < kGenRows ? K / slots : kGenRows;
+    const int rows = share > 4 ? (int)share : 4;
+    const int64_t per_launch = (int64_t(1) << 22) * rows;  // blocks x 256 inside 32 bits
+    for (int64_t row0 = 0; row0 < K; row0 += per_launch) {
+        const int64_t n = K - row0 < per_launch ? K - row0 : per_launch;
+        hipLaunchKernelGGL(k_gen_universes, dim3((unsigned)((n + rows - 1) / rows)), dim3(256), 0,
+                           st, g->S64, g->LF64, g->N, g->G, n_pts, p, seg_off, u_first, seed, row0,
+                           K, rows, d, p_idx, counts);
+    }
     return hipGetLastError();
 }
 

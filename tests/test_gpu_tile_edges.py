@@ -10,9 +10,11 @@ import pytest
 import oracle
 import parity
 from test_gpu_fixed import run_fixed
-from test_gpu_scan import FORM, fc, run_scan  # noqa: F401  (fc: fixture)
+from test_gpu_scan import FORM, fc, run_scan, to_dev  # noqa: F401  (fc: fixture)
 
 pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
 
 
 def small_problem(N, G, K, seed):
@@ -66,3 +68,39 @@ def test_fixed_matrix_groups(fc, N, iters):  # noqa: F811
     assert np.all(np.abs(dev["dchi2"] - ref["dchi2"]) <= parity.TOL["fp64"] * scale)
     for k in ("argmin", "m_final", "iters"):
         assert np.array_equal(dev[k], ref[k]), k
+
+
+# universes drawn in tiles that straddle segments and calls: one call of many
+# short segments against the oracle's counts and against calls of one segment
+@pytest.mark.parametrize("N", [1, 7, 57, 64])
+def test_universe_tiles(fc, N):  # noqa: F811
+    sizes = (1, 2, 15, 16, 17, 0, 5, 33, 4, 3000)
+    S, F, _, _ = small_problem(N, len(sizes), 1, 4)
+    S[3] *= 0.02  # means below 10: the other Poisson method
+    g = fc.fc_build_grid([np.arange(len(sizes), dtype=float)], S)
+    fc.fc_build_covariance(g, F, forms=FORM["fp32"])
+
+    def draw(pts, lens):
+        K = int(np.sum(lens))
+        d = torch.empty((K, N), dtype=torch.float64, device="cuda")
+        c = torch.empty((K, N), dtype=torch.int32, device="cuda")
+        p = torch.empty(K, dtype=torch.int64, device="cuda")
+        off = to_dev(np.concatenate([[0], np.cumsum(lens)]), torch.int64)
+        fc.fc_generate_universes(g, to_dev(pts, torch.int64), off, 11, d, p, c)
+        torch.cuda.synchronize()
+        return d.cpu().numpy(), p.cpu().numpy(), c.cpu().numpy()
+
+    pts = np.arange(len(sizes))
+    d, p, c = draw(pts, sizes)
+    assert np.array_equal(p, np.repeat(pts, sizes))
+    lo = 0
+    for q, n in zip(pts, sizes):
+        if n == 0:
+            continue
+        one, _, one_c = draw(np.array([q]), (n,))
+        assert np.array_equal(d[lo:lo + n], one) and np.array_equal(c[lo:lo + n], one_c)
+        ref, ref_c = oracle.universes(S, F, [int(q)], [0, n], 11)
+        assert np.array_equal(c[lo:lo + n], ref_c)
+        # a sum of at most 64 terms below 1e3, log and cos within an ulp or two
+        assert np.allclose(d[lo:lo + n], ref, rtol=0, atol=64 * 1e3 * 2.0 ** -50)
+        lo += n
