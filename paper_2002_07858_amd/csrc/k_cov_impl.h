@@ -10,28 +10,33 @@
 // so that Sigma_q^{-1} = W_q^T W_q and chi2 = ||W_q r||^2.  This is the step
 // whose conditioning needs FP64; the scan forms only ever see W_q.
 //
-// One wave per grid point, the matrix in registers: bins are padded to NP, a
-// multiple of four (padding rows and columns of Sigma_q are those of the
-// identity), and the kernel is instantiated per NP with every loop over rows
-// and columns unrolled, so that lane i keeps a whole row (then a whole column)
-// in NP register pairs.
-//   * Cholesky, lane i = row i of the trailing matrix: at step j every lane
-//     writes its element of column j to LDS and reads the column back as
-//     broadcasts (16-byte reads); the pivot p = A[j][j] gives
-//     L[.][j] = A[.][j] / sqrt(p), and the trailing update
-//     A[i][k] -= (A[i][j] / p) A[k][j] is one FMA per register.  The columns
-//     stay in LDS (even lengths, 16-byte aligned).
-//   * Inversion, lane i = column i of W (L w = e_i): forward substitution in
-//     axpy form over the same stored columns, w_j = s_j / L[j][j], then
-//     s_r -= L[r][j] w_j for r > j, one FMA per register.
-// Every column read is a wave-wide broadcast used by one FMA per lane: the LDS
-// reads (NP^2 / 2 doubles per point and pass) and the FP64 FMAs are of the same
-// order, and with about two waves per SIMD the per-step chain (store,
-// broadcast, pivot) is what the waves mostly wait on.  W_q
-// then goes to HBM straight from the registers (packed rows: lanes write
-// consecutive addresses) and, as packed rows, into LDS, from where each
-// requested record form is written as gathers through a per-N map
-// (fc_internal.h), one coalesced store per element.
+// One wave per grid point, the matrices in registers as 16 x 16 tiles in the
+// layout of v_mfma_f64_16x16x4_f64's output (lane l, register r: row l/16 + 4 r,
+// column l%16), bins padded to tiles with the identity's rows and columns.
+// Right-looking in panels of four columns, A the trailing part of Sigma_q and S
+// the right-hand sides of L W = 1, both lower-triangular in tiles:
+//   * the panel's four columns of A go through LDS to a lane per row; column j
+//     gives the pivot p = A[j][j], 1/sqrt(p) (the hardware estimate and two
+//     Newton steps) and 1/p as its square, m_i = A[i][j] / p, and updates the
+//     columns after it in the panel, A[i][k] -= m_i A[k][j];
+//   * the tiles right of the panel take all four columns in one MFMA each,
+//     A[i][k] += sum_j (-m_ij) A[k][j], j ascending;
+//   * the panel's four rows of S go through LDS to a lane per column:
+//     w_j = s_j / L[j][j] are rows of W, and the rows below take
+//     S[r][i] += sum_j A[r][j] (-w_ji / L[j][j]) in one MFMA per tile.
+// The FP64 MFMA adds its four products one after the other, each rounded as an
+// FMA, so every element goes through the operations of the column-by-column
+// algorithm in their order.  160 MFMAs a point at N = 57; no column of L is
+// kept.  W_q's rows go into LDS as they come, packed, and from there to HBM and,
+// gathered through a per-N map (fc_internal.h), into each requested record form,
+// in 16-byte stores.
+//
+// Measured at N = 57, 216 000 points: FP64 and FP32 forms (7.8 GB written, 1.6 ms
+// at the rate of a large copy) 6.87 ms with a lane per row and one column at a
+// time (every column read back through LDS as broadcasts, the LDS 60 % and the
+// vector units 47 % busy), 3.63 ms so; split FP16 form 7.40 and 4.15 ms.  What is
+// left is the chain of pivots (57 reciprocal roots, each after the last panel's
+// update) at two waves a SIMD, which the matrix tiles' registers allow.
 #pragma once
 #include <stdint.h>
 
@@ -39,22 +44,16 @@
 
 namespace fcx {
 
-// Column j of the factorisation in LDS: rows j .. NP-1, padded to an even count.
-__host__ __device__ constexpr int cov_col_len(int NP, int j) { return (NP - j + 1) & ~1; }
-__host__ __device__ constexpr int cov_col_off(int NP, int j)
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// LDS doubles of one point: W_q's packed rows, S_q, then two panel buffers of
+// four rows of 64 (at the end S_q - fl32(S_q) and S_q - o).
+__host__ __device__ constexpr int cov_region(int NP) { return (NP * (NP + 1) / 2 + 1) & ~1; }
+constexpr int kCovPanel = 4 * 64;
+__host__ __device__ constexpr int cov_lds_doubles(int NP)
 {
-    int o = 0;
-    for (int jj = 0; jj < j; ++jj) o += cov_col_len(NP, jj);
-    return o;
+    return cov_region(NP) + 64 + 2 * kCovPanel;
 }
-// LDS doubles of one point: the column store (later W_q's packed rows), then
-// S_q, S_q - fl32(S_q), S_q - o and 1/L[j][j], 64 each.
-__host__ __device__ constexpr int cov_region(int NP)
-{
-    return cov_col_off(NP, NP) > NP * (NP + 1) / 2 ? cov_col_off(NP, NP)
-                                                    : ((NP * (NP + 1) / 2 + 1) & ~1);
-}
-__host__ __device__ constexpr int cov_lds_doubles(int NP) { return cov_region(NP) + 4 * 64; }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -83,77 +82,78 @@ __device__ inline void split8(const float (&x)[8], uint4 &hi, uint4 &lo)
     }
 }
 
-// Materialise x here: without it the compiler may defer a register's updates
-// to its first use and keep every step's column values live until then.
-__device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
-
-// One step of either pass: a[k] = fma(-mul, c[k], a[k]) for J < k < NP, with
-// c = column J of the factorisation, read from `col` as 16-byte broadcasts in
-// chunks of kCovChunk pairs, two chunks in flight ahead of the FMAs; mul comes
-// from mulfn(first pair) (the pivot's pair).
-constexpr int kCovChunk = 3;
-
-template <int NP, int J, class MulFn>
-__device__ __forceinline__ void cov_update(const double2 *col, double (&a)[NP], MulFn mulfn)
+// The wave's LDS writes before this are seen by its reads after it (the LDS
+// serves a wave in order; this keeps the compiler's order).
+__device__ __forceinline__ void wave_lds_sync()
 {
-    constexpr int np = cov_col_len(NP, J) / 2;
-    constexpr int nch = (np + kCovChunk - 1) / kCovChunk;
-    double2 buf[2][kCovChunk];
-    static_for<0, 2 * kCovChunk>([&](auto hm) {
-        constexpr int x = decltype(hm)::value;
-        if constexpr (x < np) buf[x / kCovChunk][x % kCovChunk] = col[x];
-    });
-    const double mul = mulfn(buf[0][0]);
-    static_for<0, nch>([&](auto chc) {
-        constexpr int ch = decltype(chc)::value;
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<0, kCovChunk>([&](auto mc) {
-            constexpr int m = decltype(mc)::value;
-            constexpr int k = J + 2 * (ch * kCovChunk + m);
-            if constexpr (ch * kCovChunk + m < np) {
-                if constexpr (k > J && k < NP) {
-                    a[k] = fma(-mul, buf[ch & 1][m].x, a[k]);
-                    pin(a[k]);
-                }
-                if constexpr (k + 1 < NP) {
-                    a[k + 1] = fma(-mul, buf[ch & 1][m].y, a[k + 1]);
-                    pin(a[k + 1]);
-                }
-            }
-        });
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<0, kCovChunk>([&](auto mc) {
-            constexpr int m = decltype(mc)::value;
-            if constexpr ((ch + 2) * kCovChunk + m < np)
-                buf[ch & 1][m] = col[(ch + 2) * kCovChunk + m];
-        });
-    });
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One record element through its map entry.
-__device__ __forceinline__ double cov_gather(int m, const double *Wl, const double *Sl)
+__device__ __forceinline__ double lane_value(double x, int lane)  // lane: uniform
 {
-    return (m < 0) ? 0.0 : (m >= kMapSig ? Sl[m - kMapSig] : Wl[m]);
+    const uint2 u = __builtin_bit_cast(uint2, x);
+    return __builtin_bit_cast(double, make_uint2(__builtin_amdgcn_readlane(u.x, lane),
+                                                 __builtin_amdgcn_readlane(u.y, lane)));
+}
+
+// Map entries of a record's 16-byte units, E elements each: unit lane + 64 b in
+// en[b], all read before the record's stores (a load waits for every store
+// issued before it).
+template <int E>
+struct __attribute__((packed, aligned(4))) CovEntries {
+    int16_t m[E];
+};
+template <int E, int B>
+__device__ __forceinline__ void cov_entries(const int16_t *__restrict__ map, int units, int lane,
+                                            CovEntries<E> (&en)[B])
+{
+    const CovEntries<E> *me = reinterpret_cast<const CovEntries<E> *>(map);
+#pragma unroll
+    for (int b = 0; b < B; ++b) en[b] = me[lane + 64 * b < units ? lane + 64 * b : units - 1];
+}
+
+// The units themselves: element e comes through its entry from W_q's packed
+// rows at Lc or from S_q, `sig` doubles behind them.
+template <int E, int B, class Pack>
+__device__ __forceinline__ void cov_records(const CovEntries<E> (&en)[B], int units,
+                                            const double *Lc, int sig, int lane,
+                                            uint4 *__restrict__ rec, Pack pack)
+{
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        double v[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int m = en[b].m[e];
+            const double x = Lc[m < 0 ? 0 : (m >= kMapSig ? sig + m - kMapSig : m)];
+            v[e] = m < 0 ? 0.0 : x;
+        }
+        if (lane + 64 * b < units) rec[lane + 64 * b] = pack(v);
+    }
 }
 
 // One split-form record (see fc_internal.h) from W_q's packed rows in LDS;
 // wmax = max |W_q| (FP16 range).  Each fragment element is one gathered W_q
 // entry, scaled, rounded to the 16-bit type (hi) or, marked kMapLo, the rest
 // of that rounding (lo).
-template <bool FP16>
-__device__ void write_split_record(const double *Wl, const double *sdo, const int16_t *map, int N,
-                                   int ed, double wmax, uint4 *rq, int i)
+template <bool FP16, int B>
+__device__ __forceinline__ void write_split_record(const double *Wl, const double *sdo,
+                                                   const CovEntries<8> (&en)[B], int N, int ed,
+                                                   double wmax, uint4 *rq, int i)
 {
     const int code = split_code(N);
     const int eq = (FP16 && wmax > 0.0) ? 13 - ilogb(wmax) : 0;
     const int nf = code_nfrag(code);
-    for (int u = i; u < nf * 64; u += 64) {
-        const int16_t *mu = map + 8 * u;
+    static_for<0, B>([&](auto fc) {
+        constexpr int f = decltype(fc)::value;
+        if (f >= nf) return;  // uniform
         float x[8];
         bool lo[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int m = mu[e];
+            const int m = en[f].m[e];
             lo[e] = m >= 0 && (m & kMapLo) != 0;
             x[e] = (m < 0) ? 0.0f : (float)ldexp(Wl[m & (kMapLo - 1)], eq);
         }
@@ -168,8 +168,8 @@ __device__ void write_split_record(const double *Wl, const double *sdo, const in
             const uint32_t m1 = lo[2 * h + 1] ? 0xffff0000u : 0u;
             w[h] = (ph[h] & ~(m0 | m1)) | (pl[h] & (m0 | m1));
         }
-        rq[u] = make_uint4(w[0], w[1], w[2], w[3]);
-    }
+        rq[f * 64 + i] = make_uint4(w[0], w[1], w[2], w[3]);
+    });
     // u_q = W_q (S_q - o) in FP64, in the accumulator's row order [l/16][g][j]
     {
         const int gl = i >> 4, g = (i >> 2) & 3, j = i & 3;
@@ -177,7 +177,7 @@ __device__ void write_split_record(const double *Wl, const double *sdo, const in
         double u = 0.0;
         if (g < split_nb(N) && row < split_row0(N, g + 1)) {
             const double *wr = Wl + row * (row + 1) / 2;
-#pragma unroll 4
+#pragma unroll 8
             for (int k = 0; k <= row; ++k) u += wr[k] * sdo[k];
         }
         reinterpret_cast<float *>(rq + code_u_unit(code))[i] = (float)ldexp(-u, eq + ed);
@@ -187,8 +187,28 @@ __device__ void write_split_record(const double *Wl, const double *sdo, const in
     for (int u = su + 1 + i; u < ru; u += 64) rq[u] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// Most 16-byte units a lane holds of each record form, over the bin counts
+// N = NP-3 .. NP.
+__host__ __device__ constexpr int cov_max4(int a, int b, int c, int d)
+{
+    const int e = a > b ? a : b, f = c > d ? c : d;
+    return e > f ? e : f;
+}
+__host__ __device__ constexpr int cov_units64(int NP)
+{
+    return ceil_div(cov_max4(f64_rec_units(NP - 3), f64_rec_units(NP - 2), f64_rec_units(NP - 1),
+                             f64_rec_units(NP)),
+                    64);
+}
+__host__ __device__ constexpr int cov_units32(int NP) { return n_groups_from_ns(NP / 4); }
+__host__ __device__ constexpr int cov_units16(int NP)
+{
+    return cov_max4(code_nfrag(split_code(NP - 3)), code_nfrag(split_code(NP - 2)),
+                    code_nfrag(split_code(NP - 1)), code_nfrag(split_code(NP)));
+}
+
 template <int NP>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_cov_build(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_cov_build(
     const double *__restrict__ S64, const double *__restrict__ F, const double *__restrict__ stat,
     const double *__restrict__ off, int N_arg, int64_t G, int stat_mode, uint32_t forms, int ns,
     int ed16, const int16_t *__restrict__ maps, double *__restrict__ W64, uint4 *__restrict__ R64,
@@ -196,125 +216,211 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
     unsigned long long *__restrict__ bad_q)
 {
     static_assert(NP % 4 == 0 && NP >= 4 && NP <= 64, "NP: a multiple of four up to 64");
-    extern __shared__ double2 smem2[];
-    double *const Lc = reinterpret_cast<double *>(smem2);  // column store, then W_q's rows
-    double *const Sl = Lc + cov_region(NP);                 // S_q
-    double *const sdl = Sl + 64;                            // S_q - fl32(S_q)
-    double *const sdo = sdl + 64;                           // S_q - o
-    double *const rlv = sdo + 64;                           // 1 / L[j][j]
+    constexpr int T = (NP + 15) / 16;  // tiles a side
+    extern __shared__ double smem[];
+    double *const Lc = smem;                 // W_q's packed rows
+    double *const Sl = Lc + cov_region(NP);  // S_q
+    double *const P0 = Sl + 64;              // panel buffers [4][64]
+    double *const P1 = P0 + kCovPanel;
     const double stat_i =
         ((int)threadIdx.x < N_arg && stat_mode != FC_STAT_PEARSON) ? stat[threadIdx.x] : 0.0;
     const double off_i = ((int)threadIdx.x < N_arg) ? off[threadIdx.x] : 0.0;
 
+    const auto fetch_F = [&](v4d (&A)[T][T], int N, int g, int c) {
+        static_for<0, T>([&](auto Kc) {
+            constexpr int K = decltype(Kc)::value;
+            const int k = 16 * K + c < N ? 16 * K + c : N - 1;
+            static_for<K, T>([&](auto Ic) {
+                constexpr int I = decltype(Ic)::value;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * I + g + 4 * r;
+                    A[I][K][r] = F[k * N + (row < N ? row : N - 1)];  // F is symmetric
+                }
+            });
+        });
+    };
+    double s_next = ((int)threadIdx.x < N_arg && (int64_t)blockIdx.x < G)
+                        ? S64[(int64_t)blockIdx.x * N_arg + threadIdx.x]
+                        : 0.0;
     for (int64_t q = blockIdx.x; q < G; q += gridDim.x) {
         // the lane index and N re-read per point: everything derived from them
-        // (NP addresses and predicates) would otherwise be hoisted out of the
-        // loop and held in registers across it
+        // (addresses and predicates of NP rows) would otherwise be hoisted out
+        // of the loop and held in registers across it
         int i = threadIdx.x, N = N_arg;
         asm volatile("" : "+v"(i), "+s"(N));
+        const int g = i >> 4, c = i & 15;
         const int16_t *map64 = maps;
         const int16_t *map32 = map64 + 2 * f64_rec_units(N);
         const int16_t *map16 = map32 + 4 * rec_w_units(ns);
-        const double *Sq = S64 + q * N;
-        const double si = (i < N) ? Sq[i] : 0.0;
+        const double si = s_next;
+        v4d A[T][T];
+        fetch_F(A, N, g, c);
         Sl[i] = si;
-        sdl[i] = si - (double)(float)si;
-        sdo[i] = si - off_i;
-        __builtin_amdgcn_wave_barrier();
+        P0[i] = (i < N) ? ((stat_mode == FC_STAT_PEARSON) ? si : stat_i) : 1.0;  // diagonal term
+        wave_lds_sync();
 
-        // ---- row i of Sigma_q (F is symmetric: lanes read a column of it) ----
-        // (the column's base is re-derived per point, so that its NP addresses
-        // are not kept live across the loop over points)
-        const double *Fi = F + i;
-        double a[NP];
-        static_for<0, NP / 2>([&](auto kc) {
-            constexpr int k = 2 * decltype(kc)::value;
-            const double2 sk = smem2[cov_region(NP) / 2 + k / 2];
-            a[k] = (i < N && k < N) ? Fi[k * N] * (si * sk.x) : 0.0;
-            a[k + 1] = (i < N && k + 1 < N) ? Fi[(k + 1) * N] * (si * sk.y) : 0.0;
-            if constexpr (k % 8 == 6) __builtin_amdgcn_sched_barrier(0);  // 8 loads in flight
-        });
-        const double dg = (i < N) ? ((stat_mode == FC_STAT_PEARSON) ? si : stat_i) : 1.0;
-        static_for<0, NP>([&](auto kc) {
-            constexpr int k = decltype(kc)::value;
-            a[k] = (k == i) ? a[k] + dg : a[k];
-        });
-
-        // ---- right-looking Cholesky, lane i = row i --------------------------
-        int bad = 0;  // a pivot <= 0 or NaN (uniform)
-        static_for<0, NP>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            double *col = Lc + cov_col_off(NP, j);
-            if (i >= j && i < j + cov_col_len(NP, j)) col[i - j] = a[j];
-            __builtin_amdgcn_wave_barrier();
-            cov_update<NP, j>(reinterpret_cast<const double2 *>(col), a, [&](double2 p0) {
-                const double piv = p0.x;
-                bad |= (piv > 0.0) ? 0 : 1;
-                asm volatile("" : "+v"(bad));  // folded now, not as NP masks at the end
-                const double pv = (piv > 0.0) ? piv : 1.0;
-                // 1 / sqrt(pv): the hardware estimate and two Newton steps,
-                // y <- y (3/2 - (pv/2) y^2) (a short chain; every step waits
-                // on it), and 1 / pv as its square
-                const double h = 0.5 * pv;
-                double y = __builtin_amdgcn_rsq(pv);
-                y = y * fma(-h * y, y, 1.5);
-                y = y * fma(-h * y, y, 1.5);
-                if (i == 0) rlv[j] = y;
-                return (i > j) ? a[j] * (y * y) : 0.0;
+        // ---- Sigma_q: tiles (I, K), I >= K ---------------------------------
+        v4d S[T][T];
+        static_for<0, T>([&](auto Kc) {
+            constexpr int K = decltype(Kc)::value;
+            const int k = 16 * K + c;
+            const double sk = Sl[k], dk = P0[k];
+            static_for<K, T>([&](auto Ic) {
+                constexpr int I = decltype(Ic)::value;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+#pragma clang fp contract(off)
+                    const int row = 16 * I + g + 4 * r;
+                    double v = A[I][K][r] * (Sl[row] * sk);  // rounded before the diagonal's sum
+                    if (I == T - 1 && (row >= N || k >= N)) v = 0.0;  // (N > NP - 4)
+                    if (I == K && row == k) v = v + dk;
+                    A[I][K][r] = v;
+                }
             });
         });
-        if (bad) {  // uniform
+
+        // ---- panels of four columns ------------------------------------------
+        int bad = 0;  // a pivot <= 0 or NaN (uniform)
+        static_for<0, NP / 4>([&](auto pc) {
+            constexpr int p = decltype(pc)::value, J = p / 4, pp = p % 4;
+            // tile column J of S starts as the identity's
+            if constexpr (pp == 0)
+                static_for<J, T>([&](auto Rc) {
+                    constexpr int R = decltype(Rc)::value;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        S[R][J][r] = (R == J && g + 4 * r == c) ? 1.0 : 0.0;
+                });
+            // its columns of A, a lane per row (rows above tile J are not used),
+            // and its rows of S, a lane per column
+            wave_lds_sync();
+            if ((c >> 2) == pp)
+                static_for<J, T>([&](auto Ic) {
+                    constexpr int I = decltype(Ic)::value;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        P0[(c & 3) * 64 + 16 * I + g + 4 * r] = A[I][J][r];
+                });
+            static_for<0, J + 1>([&](auto Ic) {
+                constexpr int I = decltype(Ic)::value;
+                P1[g * 64 + 16 * I + c] = S[J][I][pp];
+            });
+            wave_lds_sync();
+            double x[4], w[4], s[4], inv[4], nm[4];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                x[a] = P0[a * 64 + i];
+                s[a] = (i < 16 * (J + 1)) ? P1[a * 64 + i] : 0.0;
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const int j = 4 * p + a;
+                const double piv = lane_value(x[a], j);
+                bad |= (piv > 0.0) ? 0 : 1;  // (its point's results are dropped)
+                // 1 / sqrt(piv): the hardware estimate and two Newton steps,
+                // y <- y (3/2 - (piv/2) y^2), and 1 / piv as its square
+                const double h = 0.5 * piv;
+                double y = __builtin_amdgcn_rsq(piv);
+                y = y * fma(-h * y, y, 1.5);
+                y = y * fma(-h * y, y, 1.5);
+                inv[a] = y * y;
+                const double m = (i > j) ? x[a] * inv[a] : 0.0;
+                w[a] = s[a] * y;
+                nm[a] = -(w[a] * y);
+#pragma unroll
+                for (int k = a + 1; k < 4; ++k) {
+                    const double akj = lane_value(x[a], 4 * p + k);
+                    x[k] = fma(-m, akj, x[k]);
+                    s[k] = fma(nm[a], akj, s[k]);
+                }
+            }
+            // operands of the tiles, panel column g: of A at row (column) 16 I + c,
+            // of S at column 16 I + c
+            wave_lds_sync();
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                P0[a * 64 + i] = x[a];
+                P1[a * 64 + i] = nm[a];
+            }
+            wave_lds_sync();
+            const double ig = g == 0 ? inv[0] : (g == 1 ? inv[1] : (g == 2 ? inv[2] : inv[3]));
+            double u[T], m[T], b[T];
+            static_for<J, T>([&](auto Ic) {
+                constexpr int I = decltype(Ic)::value;
+                u[I] = P0[g * 64 + 16 * I + c];
+                m[I] = -(u[I] * ig);
+                if constexpr (I == J) m[I] = (16 * J + c > 4 * p + g) ? m[I] : 0.0;
+            });
+            static_for<0, J + 1>([&](auto Ic) {
+                constexpr int I = decltype(Ic)::value;
+                b[I] = P1[g * 64 + 16 * I + c];
+            });
+            // the next panel's columns and rows first; tile column (row) J is done
+            // after its fourth panel
+            constexpr int J1 = J + (pp == 3 ? 1 : 0);
+            static_for<J1, T>([&](auto Kc) {
+                constexpr int K = decltype(Kc)::value;
+                static_for<K, T>([&](auto Ic) {
+                    constexpr int I = decltype(Ic)::value;
+                    A[I][K] = __builtin_amdgcn_mfma_f64_16x16x4f64(m[I], u[K], A[I][K], 0, 0, 0);
+                });
+                static_for<0, J + 1>([&](auto Ic) {
+                    constexpr int I = decltype(Ic)::value;
+                    S[K][I] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[K], b[I], S[K][I], 0, 0, 0);
+                });
+            });
+            // W_q's rows into LDS, packed (those past N, behind the rest, are not read)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const int r = 4 * p + a;
+                if (i <= r) Lc[r * (r + 1) / 2 + i] = w[a];
+            }
+        });
+        if (q + gridDim.x < G && i < N) s_next = S64[(q + gridDim.x) * N + i];
+        wave_lds_sync();
+        if (bad) {  // uniform; the build fails as a whole
             if (i == 0) atomicMin(bad_q, (unsigned long long)q);
-            __builtin_amdgcn_wave_barrier();
             continue;
         }
+        double *const sdl = P0, *const sdo = P1;
+        sdl[i] = si - (double)(float)si;  // S_q - fl32(S_q)
+        sdo[i] = si - off_i;              // S_q - o
+        wave_lds_sync();
 
-        // ---- W = L^{-1}, lane i = column i: L w = e_i -------------------------
-        // L[r][j] = c[r] rl with rl = 1 / L[j][j]: w_j = s_j rl, then
-        // s_r -= c[r] (rl w_j) for r > j
-        static_for<0, NP>([&](auto rc) {
-            constexpr int r = decltype(rc)::value;
-            a[r] = (r == i) ? 1.0 : 0.0;
-        });
-        __builtin_amdgcn_wave_barrier();
-        static_for<0, NP>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            const double rl = rlv[j];
-            cov_update<NP, j>(reinterpret_cast<const double2 *>(Lc + cov_col_off(NP, j)), a,
-                              [&](double2) {
-                                  const double w = a[j] * rl;
-                                  a[j] = w;
-                                  return w * rl;
-                              });
-        });
-
-        // ---- W_q: HBM (packed rows) and LDS (packed rows, over the columns) ----
-        double wmax = 0.0;
-        double *Wq = (forms & FC_FORM_FP64) ? W64 + q * ((int64_t)N * (N + 1) / 2) : nullptr;
-        __builtin_amdgcn_wave_barrier();
-        static_for<0, NP>([&](auto rc) {
-            constexpr int r = decltype(rc)::value;
-            if (r < N && i <= r) {
-                const int at = r * (r + 1) / 2 + i;
-                Lc[at] = a[r];
-                if (Wq) Wq[at] = a[r];
-                wmax = fmax(wmax, fabs(a[r]));
+        // ---- W_q: the packed rows to HBM -----------------------------------------
+        if (forms & FC_FORM_FP64) {
+            const int nt = N * (N + 1) / 2;
+            double *Wq = W64 + q * nt;
+            constexpr int B = 13;  // stores prepared at a time
+            for (int e0 = i; e0 < nt; e0 += 64 * B) {
+                double v[B];
+#pragma unroll
+                for (int k = 0; k < B; ++k) v[k] = Lc[e0 + 64 * k < nt ? e0 + 64 * k : 0];
+#pragma unroll
+                for (int k = 0; k < B; ++k)
+                    if (e0 + 64 * k < nt) Wq[e0 + 64 * k] = v[k];
             }
-            if constexpr (r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
-        });
-        __builtin_amdgcn_wave_barrier();
-
+        }
         // ---- the requested record forms ----------------------------------------
         if (forms & FC_FORM_FP64) {
-            double *rq = reinterpret_cast<double *>(R64 + q * (int64_t)f64_rec_units(N));
-            const int n = 2 * f64_rec_units(N);
-            for (int e = i; e < n; e += 64) rq[e] = cov_gather(map64[e], Lc, Sl);
+            CovEntries<2> m64[cov_units64(NP)];
+            cov_entries(map64, f64_rec_units(N), i, m64);
+            cov_records(m64, f64_rec_units(N), Lc, cov_region(NP), i,
+                        R64 + q * (int64_t)f64_rec_units(N), [](const double (&v)[2]) {
+                            return __builtin_bit_cast(uint4, make_double2(v[0], v[1]));
+                        });
         }
         if (forms & FC_FORM_FP32) {
             uint4 *rq = R32 + q * (int64_t)rec_units(ns);
-            float *Wf = reinterpret_cast<float *>(rq);
-            const int n = 4 * rec_w_units(ns);
-            for (int e = i; e < n; e += 64) Wf[e] = (float)cov_gather(map32[e], Lc, Sl);
+            CovEntries<4> m32[cov_units32(NP)];
+            cov_entries(map32, rec_w_units(ns), i, m32);
+            cov_records(m32, rec_w_units(ns), Lc, cov_region(NP), i, rq,
+                        [](const double (&v)[4]) {
+                            return __builtin_bit_cast(uint4,
+                                                      make_float4((float)v[0], (float)v[1],
+                                                                  (float)v[2], (float)v[3]));
+                        });
             // FP32 part of the signal (real bin order), then minus W_q times
             // its rounding error (padded row order)
             float *Sp = reinterpret_cast<float *>(rq + rec_w_units(ns));
@@ -323,20 +429,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
             double cv = 0.0;
             if (rr >= 0 && rr < N) {
                 const double *wr = Lc + rr * (rr + 1) / 2;
-#pragma unroll 4
+#pragma unroll 8
                 for (int kk = 0; kk <= rr; ++kk) cv -= wr[kk] * sdl[kk];
             }
             Sp[64 + i] = (float)cv;
         }
         if (forms & (FC_FORM_SPLIT_BF16 | FC_FORM_SPLIT_FP16)) {
-            for (int m = 32; m > 0; m >>= 1) wmax = fmax(wmax, __shfl_xor(wmax, m));
+            CovEntries<8> m16[cov_units16(NP)];
+            cov_entries(map16, code_nfrag(split_code(N)) * 64, i, m16);
+            double wmax = 0.0;  // FP16's scale
+            if (forms & FC_FORM_SPLIT_FP16) {
+                for (int e = i; e < N * (N + 1) / 2; e += 64) wmax = fmax(wmax, fabs(Lc[e]));
+                for (int m = 32; m > 0; m >>= 1) wmax = fmax(wmax, __shfl_xor(wmax, m));
+            }
             const int64_t sru = split_rec_units(N);
             if (forms & FC_FORM_SPLIT_BF16)
-                write_split_record<false>(Lc, sdo, map16, N, 0, wmax, RB16 + q * sru, i);
+                write_split_record<false>(Lc, sdo, m16, N, 0, wmax, RB16 + q * sru, i);
             if (forms & FC_FORM_SPLIT_FP16)
-                write_split_record<true>(Lc, sdo, map16, N, ed16, wmax, RH16 + q * sru, i);
+                write_split_record<true>(Lc, sdo, m16, N, ed16, wmax, RH16 + q * sru, i);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();  // before the next point's LDS writes
     }
 }
 

@@ -1,6 +1,6 @@
 """The scans at the edges of their tilings: bin counts at the borders of the
-kernels' row groups, universe counts at the borders of their tiles, grids of
-one, two and a few points, against the FP64 oracle (tolerances of the forms,
+kernels' row groups and of the factorisation's tiles, universe counts at the
+borders of their tiles, grids of one, two and a few points, against the FP64 oracle (tolerances of the forms,
 as everywhere)."""
 from __future__ import annotations
 
@@ -104,3 +104,30 @@ def test_universe_tiles(fc, N):  # noqa: F811
         # a sum of at most 64 terms below 1e3, log and cos within an ulp or two
         assert np.allclose(d[lo:lo + n], ref, rtol=0, atol=64 * 1e3 * 2.0 ** -50)
         lo += n
+
+
+# covariances at the borders of the factorisation's tiles (16 rows) and panels
+# (4 columns): W^T W against LAPACK's inverse, and a zero pivot in the
+# first and the last bin found at its point
+@pytest.mark.parametrize("N", [1, 2, 4, 15, 16, 17, 31, 32, 33, 44, 47, 48, 49, 57, 60, 63, 64])
+def test_covariance_tiles(fc, N):  # noqa: F811
+    G = 9
+    S, F, _, _ = small_problem(N, G, 1, 5)
+    stat = np.linspace(20.0, 500.0, N)
+    g = fc.fc_build_grid([np.arange(G, dtype=float)], S)
+    fc.fc_build_covariance(g, F, fc.FC_STAT_FIXED, stat, forms=FORM["fp64"])
+    out = torch.empty((G, N, N), dtype=torch.float64, device="cuda")
+    fc.fc_grid_inverse_cov(g, 0, G, out)
+    torch.cuda.synchronize()
+    for q in range(G):
+        sig = oracle.covariance(S[q], F, oracle.STAT_FIXED, stat)
+        ref = np.linalg.inv(sig)
+        err = np.linalg.norm(out[q].cpu().numpy() - ref) / np.linalg.norm(ref)
+        assert err <= 1e-12 * np.linalg.cond(sig), (q, err)
+    for b in {0, N - 1}:
+        Z = S.copy()
+        Z[4:, b] = 0.0
+        g = fc.fc_build_grid([np.arange(G, dtype=float)], Z)
+        with pytest.raises(fc.FCError) as ei:
+            fc.fc_build_covariance(g, F, fc.FC_STAT_FIXED, np.zeros(N), forms=FORM["fp64"])
+        assert ei.value.code == fc.FC_ERR_NOT_PD and ei.value.bad_q == 4
