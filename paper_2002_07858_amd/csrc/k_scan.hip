@@ -71,9 +71,18 @@ __device__ __forceinline__ float fma_mix_dl(uint32_t dl2, float scale, float t)
 
 // Sums of squares over row blocks B0 .. B1-1 into the lane's four FP32 chains
 // (one per row of a block; the P padding rows of block 0 are zero and skipped).
+// A single block's are added up as FMAs.
 template <int P, int B0, int B1, int NS>
 __device__ __forceinline__ void fp32_squares(const v4f (&acc)[NS], float (&part)[4])
 {
+    if constexpr (NS == 1) {
+        const v4f z = acc[0];
+        part[1] = part[3] = 0.0f;
+        part[0] = P < 1 ? fmaf(z[0], z[0], z[1] * z[1]) : 0.0f;
+        part[2] = P < 3 ? fmaf(z[2], z[2], z[3] * z[3]) : z[3] * z[3];
+        if constexpr (P == 1) part[2] = fmaf(z[1], z[1], part[2]);
+        return;
+    }
     static_for<B0, B1>([&](auto bc) {
         constexpr int b = decltype(bc)::value;
 #pragma unroll
