@@ -13,6 +13,7 @@
 // (universe, grid point) is the same code as fc_scan, and the running minimum
 // is merged with an order-independent atomicMin, so a request's results do
 // not depend on the mix it ran in.
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
@@ -52,7 +53,26 @@ int fail(int code, const char *fmt, ...)
 
 constexpr int kMaxItems = 16384;   // items per batched launch
 constexpr int64_t kMaxK = int64_t(1) << 20;
-constexpr int64_t kQStep = 256;     // grid points per item
+
+// Grid points per work item.  An item starts by loading its tile's universes
+// and its first record, so it must not be short; but a launch's blocks end up
+// to one item apart, and with two FP32 blocks a CU a point takes 4.2 us.  The
+// split forms' points are three times as fast and their start (the universes'
+// fragments) is longer.  Where the requests at hand would give a resident block
+// fewer than kItemsPerSlot items of the largest length, they are cut into that
+// many, down to the least length.
+// Measured, largest length 256 / 128 / 64: FP32, 24 requests of 500 to 20 000
+// universes (100 x 100 points of 57 bins, 20 x 20 of 38) 34.2 / 31.7 / 31.7 ms;
+// 40 of 100 to 3000 (60 x 60 and 30 x 30 points of 57) 6.8 / 5.9 / 5.8 ms; split
+// BF16, 20 of 1000 to 20 000 (100 x 100 of 57, 60 x 60 of 38) 11.6 / 12.1 ms / -.
+// Two requests of about 550 (100 x 100 of 57, 20 x 20 of 38): FP32 1.26 ms in
+// items of 256, 0.98 of 128, 0.86 cut to 32 (and to 16); split FP16 0.85 of 256,
+// 0.61 of 128, 0.86 cut to 32 as a block loads its universes too often.
+struct ItemLen {
+    int64_t least, largest;
+};
+constexpr ItemLen kItemLenFp32{32, 128}, kItemLenSplit{128, 256};
+constexpr int kItemsPerSlot = 2;
 
 // First-fit allocator of offsets inside one fixed region.
 class Arena {
@@ -312,6 +332,12 @@ bool fc_server::launch(Cls &c)
     std::vector<Req *> completing;
     // FAIR: one range of grid points per request per round; FIFO: a request
     // takes ranges until it is fully scheduled before the next one is served
+    double work = 0.0;  // (tile, grid point) pairs at hand
+    for (const Req *r : order)
+        work += (double)((r->K + c.upi - 1) / c.upi) * (double)(grids[r->grid]->G - r->q_next);
+    const ItemLen len = (form == FC_FORM_FP32) ? kItemLenFp32 : kItemLenSplit;
+    const int64_t step = std::max(
+        len.least, (int64_t)std::min((double)len.largest, work / (kItemsPerSlot * c.slots)));
     bool any = true;
     while (any && budget > 0.0 && n < kMaxItems) {
         any = false;
@@ -322,7 +348,7 @@ bool fc_server::launch(Cls &c)
             const int64_t ntiles = (r->K + c.upi - 1) / c.upi;
             if (n + ntiles > kMaxItems) continue;
             const int64_t qb = r->q_next;
-            const int64_t qe = (qb + kQStep < g->G) ? qb + kQStep : g->G;
+            const int64_t qe = (qb + step < g->G) ? qb + step : g->G;
             for (int64_t t = 0; t < ntiles; ++t) {
                 fcx::ScanItem &it = items[n++];
                 it.R = (form == FC_FORM_FP32) ? g->R32 : (form == FC_FORM_SPLIT_FP16 ? g->RH16 : g->RB16);

@@ -4,6 +4,8 @@ borders of their tiles, grids of one, two and a few points, against the FP64 ora
 as everywhere)."""
 from __future__ import annotations
 
+import time
+
 import numpy as np
 import pytest
 
@@ -131,3 +133,35 @@ def test_covariance_tiles(fc, N):  # noqa: F811
         with pytest.raises(fc.FCError) as ei:
             fc.fc_build_covariance(g, F, fc.FC_STAT_FIXED, np.zeros(N), forms=FORM["fp64"])
         assert ei.value.code == fc.FC_ERR_NOT_PD and ei.value.bad_q == 4
+
+
+# served requests whose items are cut to the least length, to one in between
+# and to the largest, on grids of less than one item, of one, and with a
+# remainder: bit for bit fc_scan's results
+@pytest.mark.parametrize("form", ["fp32", "split_bf16", "split_fp16"])
+@pytest.mark.parametrize("G,sizes", [(1, (1, 300)), (31, (1,)), (33, (255, 257)), (129, (1, 2, 3)),
+                                     (5000, (1, 700)), (20011, (5000, 1, 3000))])
+def test_served_items(fc, form, G, sizes):  # noqa: F811
+    N = 19
+    S, F, p, d = small_problem(N, G, sum(sizes), 6)
+    g = fc.fc_build_grid([np.arange(G, dtype=float)], S)
+    fc.fc_build_covariance(g, F, forms=FORM[form])
+    srv = fc.Server([g], form=FORM[form], hbm_budget=64 << 20, host_budget=64 << 20)
+    try:
+        lo, ids = 0, []
+        for n in sizes:
+            ids.append(srv.submit(0, int(p[lo]), d[lo:lo + n]))
+            lo += n
+        lo = 0
+        for i, n in zip(ids, sizes):
+            state, got = srv.poll(i)
+            while got is None:
+                assert state != fc.FC_REQ_FAILED
+                time.sleep(1e-4)
+                state, got = srv.poll(i)
+            ref = run_scan(fc, g, FORM[form], d[lo:lo + n], np.full(n, p[lo]))
+            for k in ("dchi2", "chi2_min", "argmin", "chi2_p"):
+                assert np.array_equal(got[k], ref[k]), (n, k)
+            lo += n
+    finally:
+        srv.destroy()
