@@ -90,7 +90,8 @@ WORKLOADS = {
 # WRITE_SIZE passes scaled by the same counters over a copy of known size
 # (the profiles directory holds the summaries).  Valid only while the kernel's
 # sources hash to the value the counters were taken with.
-FP32_SOURCES = ("paper_2002_07858_amd/csrc/k_scan.hip", "paper_2002_07858_amd/csrc/fc_internal.h")
+FP32_SOURCES = tuple("paper_2002_07858_amd/csrc/" + f for f in
+                     ("k_scan_fp32.h", "k_scan.hip", "k_scan_pts.hip", "fc_internal.h"))
 SPLIT_SOURCES = ("paper_2002_07858_amd/csrc/k_scan_split.hip",
                  "paper_2002_07858_amd/csrc/fc_internal.h")
 FP64_SOURCES = ("paper_2002_07858_amd/csrc/k_scan64.hip",

@@ -297,13 +297,15 @@ struct Fp64Part {
 // for (I = B; I < E; ++I) fn(integral_constant<I>), expanded at compile time
 // (loops over registers must be unrolled for their indices to be static; the
 // unroller gives up on the larger ones).
+template <int B, class Fn, int... I>
+__device__ __forceinline__ void static_for_seq(Fn &fn, std::integer_sequence<int, I...>)
+{
+    (fn(std::integral_constant<int, B + I>{}), ...);
+}
 template <int B, int E, class Fn>
 __device__ __forceinline__ void static_for(Fn &&fn)
 {
-    if constexpr (B < E) {
-        fn(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(fn);
-    }
+    static_for_seq<B>(fn, std::make_integer_sequence<int, (E > B ? E - B : 0)>{});
 }
 
 // Copy one record of REC 16-byte units into LDS with direct global -> LDS
