@@ -99,18 +99,18 @@ FP64_SOURCES = ("paper_2002_07858_amd/csrc/k_scan64.hip",
 # FETCH_SIZE (KiB x 1024 x 2.0000) + WRITE_SIZE (KiB x 1024 x 1.0000) of one launch
 # (a leg's: mean of the three launches of one run)
 TRAFFIC = {
-    ("c5", "fp64", "points"): {"bytes_per_launch": 985414308 * 2048 + 1281250 * 1024,
-                               "source_hash": "7c799a98aa98fe16", "sources": FP64_SOURCES,
-                               "profile": "profiles/k_scan_f64m_c5.md"},
-    ("c5", "fp32", "points"): {"bytes_per_launch": 227249134 * 2048 + 641250 * 1024,
-                               "source_hash": "37a4a054150dd848", "sources": FP32_SOURCES,
-                               "profile": "profiles/k_scan_c5_fp32_split_counters.md"},
-    ("c5", "split_fp16", "points"): {"bytes_per_launch": 2194617926 * 2048 + 2561250 * 1024,
-                                     "source_hash": "98549ac6fbe21dfe", "sources": SPLIT_SOURCES,
-                                     "profile": "profiles/k_scan_c5_fp32_split_counters.md"},
-    ("c5", "split_bf16", "points"): {"bytes_per_launch": 568374400 * 2048 + 6721251 * 1024,
-                                     "source_hash": "98549ac6fbe21dfe", "sources": SPLIT_SOURCES,
-                                     "profile": "profiles/k_scan_c5_fp32_split_counters.md"},
+    ("c5", "fp64", "points"): {"bytes_per_launch": 413668829 * 2048 + 2781250 * 1024,
+                               "source_hash": "89f6d98ab5b6b439", "sources": FP64_SOURCES,
+                               "profile": "profiles/c5_all_forms.md"},
+    ("c5", "fp32", "points"): {"bytes_per_launch": 135335341 * 2048 + 641250 * 1024,
+                               "source_hash": "0bc2e426ebb2b1ce", "sources": FP32_SOURCES,
+                               "profile": "profiles/c5_all_forms.md"},
+    ("c5", "split_fp16", "points"): {"bytes_per_launch": 2072373524 * 2048 + 2561250 * 1024,
+                                     "source_hash": "05fc610e0c577218", "sources": SPLIT_SOURCES,
+                                     "profile": "profiles/c5_all_forms.md"},
+    ("c5", "split_bf16", "points"): {"bytes_per_launch": 561525370 * 2048 + 6721251 * 1024,
+                                     "source_hash": "05fc610e0c577218", "sources": SPLIT_SOURCES,
+                                     "profile": "profiles/c5_all_forms.md"},
 }
 
 

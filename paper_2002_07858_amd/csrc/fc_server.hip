@@ -58,21 +58,24 @@ constexpr int64_t kMaxK = int64_t(1) << 20;
 // and its first record, so it must not be short; but a launch's blocks end up
 // to one item apart, and with two FP32 blocks a CU a point takes 4.2 us.  The
 // split forms' points are three times as fast and their start (the universes'
-// fragments) is longer.  Where the requests at hand would give a resident block
-// fewer than kItemsPerSlot items of the largest length, they are cut into that
-// many, down to the least length.
+// fragments) is longer: twice the length, which FP32 also takes while the requests
+// at hand fill many launches (more than kLongQueue points a block slot).
+// Where they would give a resident block fewer than kItemsPerSlot items of the
+// largest length, they are cut into that many, down to the least length.
 // Measured, largest length 256 / 128 / 64: FP32, 24 requests of 500 to 20 000
 // universes (100 x 100 points of 57 bins, 20 x 20 of 38) 34.2 / 31.7 / 31.7 ms;
 // 40 of 100 to 3000 (60 x 60 and 30 x 30 points of 57) 6.8 / 5.9 / 5.8 ms; split
 // BF16, 20 of 1000 to 20 000 (100 x 100 of 57, 60 x 60 of 38) 11.6 / 12.1 ms / -.
+// 24 of 500 to 20 000 on 60^3 and 20^3 points of 57: FP32 417.7 / 422.7 ms / -.
 // Two requests of about 550 (100 x 100 of 57, 20 x 20 of 38): FP32 1.26 ms in
 // items of 256, 0.98 of 128, 0.86 cut to 32 (and to 16); split FP16 0.85 of 256,
 // 0.61 of 128, 0.86 cut to 32 as a block loads its universes too often.
 struct ItemLen {
-    int64_t least, largest;
+    int64_t least, largest, long_queue;
 };
-constexpr ItemLen kItemLenFp32{32, 128}, kItemLenSplit{128, 256};
+constexpr ItemLen kItemLenFp32{32, 128, 256}, kItemLenSplit{128, 256, 256};
 constexpr int kItemsPerSlot = 2;
+constexpr double kLongQueue = 16384.0;
 
 // First-fit allocator of offsets inside one fixed region.
 class Arena {
@@ -336,8 +339,10 @@ bool fc_server::launch(Cls &c)
     for (const Req *r : order)
         work += (double)((r->K + c.upi - 1) / c.upi) * (double)(grids[r->grid]->G - r->q_next);
     const ItemLen len = (form == FC_FORM_FP32) ? kItemLenFp32 : kItemLenSplit;
-    const int64_t step = std::max(
-        len.least, (int64_t)std::min((double)len.largest, work / (kItemsPerSlot * c.slots)));
+    const double share = work / c.slots;
+    const int64_t most = share > kLongQueue ? len.long_queue : len.largest;
+    const int64_t step =
+        std::max(len.least, (int64_t)std::min((double)most, share / kItemsPerSlot));
     bool any = true;
     while (any && budget > 0.0 && n < kMaxItems) {
         any = false;

@@ -26,7 +26,7 @@
 //     S[r][i] += sum_j A[r][j] (-w_ji / L[j][j]) in one MFMA per tile.
 // The FP64 MFMA adds its four products one after the other, each rounded as an
 // FMA, so every element goes through the operations of the column-by-column
-// algorithm in their order.  160 MFMAs a point at N = 57; no column of L is
+// algorithm in their order.  135 MFMAs a point at N = 57; no column of L is
 // kept.  W_q's rows go into LDS as they come, packed, and from there to HBM and,
 // gathered through a per-N map (fc_internal.h), into each requested record form,
 // in 16-byte stores.

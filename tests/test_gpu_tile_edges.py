@@ -140,7 +140,7 @@ def test_covariance_tiles(fc, N):  # noqa: F811
 # remainder: bit for bit fc_scan's results
 @pytest.mark.parametrize("form", ["fp32", "split_bf16", "split_fp16"])
 @pytest.mark.parametrize("G,sizes", [(1, (1, 300)), (31, (1,)), (33, (255, 257)), (129, (1, 2, 3)),
-                                     (5000, (1, 700)), (20011, (5000, 1, 3000))])
+                                     (5000, (1, 700)), (20011, (5000, 1, 3000)), (70001, (31000, 1))])
 def test_served_items(fc, form, G, sizes):  # noqa: F811
     N = 19
     S, F, p, d = small_problem(N, G, sum(sizes), 6)
