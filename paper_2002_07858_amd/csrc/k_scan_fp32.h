@@ -23,8 +23,9 @@
 // point at two waves per SIMD.  The launch is then bound by power: the matrix
 // cores are 92 % busy at 2.22 GHz (85 % at 2.31 GHz before; offset form, 100 x
 // 100 points, N = 57, 256 x 2000 universes: 142.1 -> 137.3 ms; residual form,
-// 27 000 points x 20 000 universes: 17.4 -> 16.9 ms; three waves per SIMD with
-// the universes' low parts in LDS 16.9-17.1 ms).
+// 27 000 points x 20 000 universes: 17.4 -> 16.9 ms, 216 000 points the same at
+// 128.6 ms; three waves per SIMD with the universes' low parts in LDS
+// 16.9-17.1 ms).
 //
 // Work decomposition: a 256-thread block owns 256 universes (one per lane)
 // and walks a contiguous range of grid points in list order.  Each lane
