@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "fc.h"
+#include "scan_geometry.h"
 
 // ---------------------------------------------------------------------------
 // FP32 factor layout for the MFMA scan.
@@ -599,17 +600,5 @@ hipError_t launch_data_scan(const fc_grid *g, const double *c, double *chi2,
                             unsigned long long *scratch, hipStream_t st);
 hipError_t launch_accept(int64_t n_pts, const int64_t *p, const double *crit, int64_t stride,
                          const double *dchi2_data, int64_t G, uint8_t *accepted, hipStream_t st);
-
-// Scan launch geometry chosen by the host: n_utiles universe tiles, each against
-// n_qchunks grid chunks of q_per_chunk points (the last one shorter).
-struct ScanGeometry {
-    int64_t n_utiles = 0;
-    int64_t n_qchunks = 0;
-    int64_t q_per_chunk = 0;
-};
-// n_utiles tiles of which about `tiles` have work, G grid points, `slots`
-// resident blocks, at most max_chunks chunks.
-ScanGeometry scan_geometry(int64_t n_utiles, int64_t tiles, int64_t G, int slots,
-                           int64_t max_chunks);
 
 }  // namespace fcx

@@ -585,7 +585,7 @@ struct FxLaunch {
     void chunks(int64_t G, int slots)
     {
         const int64_t steps = (G + kFxTile - 1) / kFxTile;
-        const ScanGeometry sg = scan_geometry(n_tiles, n_tiles, steps, slots, steps);
+        const ScanGeometry sg = scan_geometry(n_tiles, n_tiles, steps, slots, steps, kPointsChunks);
         q_per_chunk = sg.q_per_chunk * kFxTile;
         n_chunks = (int)sg.n_qchunks;
     }

@@ -1,8 +1,6 @@
-// k_scan.hip -- the FP32 scan in the residual form (k_scan_fp32.h), the geometry
-// of every scan, and the start and the end of the running minima.
+// k_scan.hip -- the FP32 scan in the residual form (k_scan_fp32.h), and the start
+// and the end of the running minima.
 #include "k_scan_fp32.h"
-
-#include <algorithm>
 
 namespace fcx {
 
@@ -94,41 +92,6 @@ int resident_slots(const void *kernel, int block_threads)
     return cus * per_cu;
 }
 
-// Grid chunks of a scan.  All blocks of a launch take about the same time, one
-// chunk each, so the launch takes rounds(c) = ceil(tiles c / slots) of them and
-// a half-empty last round is lost; c is the count that minimises
-//     rounds(c) (points per chunk + kChunkCost),
-// kChunkCost being a block's start (staging its universes) in points.  Chunks
-// are at most kChunkMax points long, so that the blocks that share a chunk stay
-// close and the L2 serves the later readers of each record, and at least
-// kChunkMin, which sets how far a small scan spreads over the CUs.  (FP64, 1000
-// tiles x 10 000 points on 768 slots: 5 chunks in 6.5 rounds 67.6 ms, 23 in
-// 29.95 rounds 65.2 ms; split FP16, 20 tiles x 216 000 points on 512 slots: 106
-// chunks in 4.1 rounds 12.7 ms, 128 in 5.0 rounds 11.0 ms.)
-ScanGeometry scan_geometry(int64_t n_utiles, int64_t tiles, int64_t G, int slots,
-                           int64_t max_chunks)
-{
-    constexpr int64_t kChunkMax = 2048, kChunkMin = 4, kChunkCost = 2;
-    ScanGeometry sg;
-    sg.n_utiles = n_utiles;
-    // blocks x 256 work-items stay well inside the 32-bit dispatch size
-    const int64_t fit = (int64_t(1) << 23) / std::max<int64_t>(n_utiles, 1);
-    const int64_t cap = std::max<int64_t>(1, std::min(max_chunks, fit));
-    const int64_t lo = std::min(cap, (G + kChunkMax - 1) / kChunkMax);
-    const int64_t hi = std::min(cap, std::max(lo, std::min(G / kChunkMin, 2 * lo + 512)));
-    int64_t best = INT64_MAX;
-    for (int64_t c = lo; c <= hi; ++c) {
-        const int64_t q = (G + c - 1) / c, n = (G + q - 1) / q;
-        const int64_t cost = (tiles * n + slots - 1) / slots * (q + kChunkCost);
-        if (cost < best) {
-            best = cost;
-            sg.q_per_chunk = q;
-            sg.n_qchunks = n;
-        }
-    }
-    return sg;
-}
-
 template <int N>
 static hipError_t launch_fp32_n(const fc_grid *g, int64_t K, const double *d, const int64_t *p_idx,
                                 int64_t q0, int64_t nq, unsigned long long *keys, double *chi2_p,
@@ -138,7 +101,7 @@ static hipError_t launch_fp32_n(const fc_grid *g, int64_t K, const double *d, co
     static const int slots =
         resident_slots(reinterpret_cast<const void *>(&k_scan_fp32<N>), 64 * kWavesPerBlock);
     const int64_t tiles = (K + kFp32UnivPerBlock - 1) / kFp32UnivPerBlock;
-    const ScanGeometry sg = scan_geometry(tiles, tiles, nq, slots, nq);
+    const ScanGeometry sg = scan_geometry(tiles, tiles, nq, slots, nq, kScanChunks);
     const int64_t blocks = sg.n_utiles * sg.n_qchunks;
     ProfScope prof(st, "k_scan_fp32");
     hipLaunchKernelGGL((k_scan_fp32<N>), dim3((unsigned)blocks), dim3(64 * kWavesPerBlock), 0, st,

@@ -49,6 +49,11 @@ constexpr int kF64Waves = 4;                       // waves per block
 constexpr int kF64Sets = 2;                        // sets of 16 universes per wave
 constexpr int kF64Univ = 16 * kF64Sets * kF64Waves;  // universes per block (128)
 constexpr size_t kF64PartsMax = size_t(2) << 30;      // bytes of chunk partials at most
+// Partials past 2 MiB are mapped anew on each call of a caller that waits in
+// between: 36 us, about 32 points of a full chip (2000 universes x 400 points of
+// 20 bins: 80 chunks 75 us, 64 chunks 41 us).
+constexpr int64_t kF64PartsSoft = int64_t(2) << 20;
+constexpr double kF64PartsCost = 32.0;
 
 constexpr int kF64Ahead = 2;  // tile pairs read from LDS ahead of their MFMAs
 
@@ -323,8 +328,12 @@ hipError_t launch_f64m_n(const fc_grid *g, int64_t K, const double *d, const int
         resident_slots(reinterpret_cast<const void *>(&k_scan_f64m<N>), 64 * kF64Waves);
     const int64_t G = g->G;
     const int64_t tiles = (K + kF64Univ - 1) / kF64Univ;
-    const ScanGeometry sg = scan_geometry(
-        tiles, tiles, G, slots, (int64_t)(kF64PartsMax / (sizeof(Fp64Part) * (size_t)K)));
+    const int64_t chunk_bytes = (int64_t)sizeof(Fp64Part) * K;
+    ChunkRule rule = kFp64Chunks;
+    rule.soft_chunks = std::max<int64_t>(1, kF64PartsSoft / chunk_bytes);
+    rule.soft_cost = kF64PartsCost;
+    const ScanGeometry sg =
+        scan_geometry(tiles, tiles, G, slots, (int64_t)kF64PartsMax / chunk_bytes, rule);
     int64_t chunks = sg.n_qchunks, qpc = sg.q_per_chunk;
     // the partials must fit the scratch (library-owned or the caller's)
     const int64_t max_chunks = (int64_t)(scratch_bytes / (sizeof(Fp64Part) * (size_t)K));

@@ -156,7 +156,7 @@ static hipError_t launch_fp32_pts_n(const fc_grid *g, int64_t n_pts, const int64
     // known on the device only)
     const int64_t len = (K + n_pts - 1) / n_pts;
     const int64_t tiles = std::min(max_tiles, n_pts * ((len + kPtsTile - 1) / kPtsTile));
-    const ScanGeometry sg = scan_geometry(n_tiles, tiles, nq, slots, nq);
+    const ScanGeometry sg = scan_geometry(n_tiles, pts_busy_tiles(tiles), nq, slots, nq, kPointsChunks);
     const int64_t blocks = n_tiles * sg.n_qchunks;
     hipLaunchKernelGGL(k_tile_prefix, dim3(1), dim3(1024), 0, st, n_pts, seg_off, tile_start);
     ProfScope prof(st, "k_scan_fp32_pts");

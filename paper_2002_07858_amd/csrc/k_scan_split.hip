@@ -453,7 +453,7 @@ static hipError_t launch_split_t(const fc_grid *g, int64_t K, const double *d,
         resident_slots_split(reinterpret_cast<const void *>(&k_scan_split<CODE, NC, FP16>));
     constexpr int64_t tile = 16 * NC * kWavesPerBlock;
     const int64_t tiles = (K + tile - 1) / tile;
-    const ScanGeometry sg = scan_geometry(tiles, tiles, nq, slots, nq);
+    const ScanGeometry sg = scan_geometry(tiles, tiles, nq, slots, nq, kScanChunks);
     const int64_t blocks = sg.n_utiles * sg.n_qchunks;
     const uint4 *R = FP16 ? g->RH16 : g->RB16;
     ProfScope prof(st, "k_scan_split");
