@@ -39,22 +39,13 @@
 // Per-chunk minima (value, q) are merged by a small kernel with Algorithm 1's
 // rule (smallest value, then lowest q).
 #include "fc_internal.h"
-
-#include <algorithm>
-#include <vector>
+#include "fixed_plan.h"
 
 namespace fcx {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int kFxTile = 64;      // universes per block, grid points per step
 constexpr int kFxThreads = 256;
-// Groups up to this size go to k_fixed_small; larger ones share a t table
-// (64 groups of n universes, 10 000 points, N = 57, the whole call, the best of
-// three: n = 128 0.67 ms against 0.92 with tables, 192 0.92 against 1.07, 256
-// 1.11 against 2.95, 512 2.03 against 1.73; N = 20 on 3600 points: 128 0.24
-// against 0.26, 256 0.39 against 0.37).
-constexpr int kFxSmall = 256;
 
 // y = W_m (d - o), a = ||y||^2 for universe rows in group order: one wave per
 // row, lane i = component i (zero past N, stored padded to 4 * ns).
@@ -144,12 +135,6 @@ __global__ __launch_bounds__(256) void k_fixed_t(const double *__restrict__ W64,
     }
 }
 
-struct FxTileDesc {
-    int64_t r0;     // first row (group order) of the tile
-    int32_t n;      // rows in the tile (1..64; k_fixed_small: 1..16 NU)
-    int32_t slot;   // matrix slot of the group (k_fixed_small: the matrix's grid point)
-};
-
 // X = S - o in the B-operand order of k_fixed_small: Xt[q / 16][s][lane] holds
 // grid point q = 16 (q / 16) + lane % 16, bin 4 s + lane / 16 (zero past G and N).
 __global__ __launch_bounds__(256) void k_fixed_x(const double *__restrict__ S64,
@@ -164,21 +149,6 @@ __global__ __launch_bounds__(256) void k_fixed_x(const double *__restrict__ S64,
     Xt[e] = (q < G && j < N) ? S64[q * N + j] - off[j] : 0.0;
 }
 
-// Candidates of one row: cand[row][stride] holds the kernel's n_chunks values
-// and +inf past them (the kernels of one round take different chunk counts).
-__device__ __forceinline__ void fixed_candidate(double *__restrict__ cand_v,
-                                                int64_t *__restrict__ cand_q, int64_t r, int stride,
-                                                int chunk, int n_chunks, double v, int64_t q)
-{
-    cand_v[r * stride + chunk] = v;
-    cand_q[r * stride + chunk] = q;
-    if (chunk + 1 == n_chunks)
-        for (int c = n_chunks; c < stride; ++c) {
-            cand_v[r * stride + c] = __builtin_inf();
-            cand_q[r * stride + c] = INT64_MAX;
-        }
-}
-
 // Running minimum of one tile of at most 16 NU universes of one matrix against
 // the grid points of one chunk; outputs as k_fixed_min.  W_m stays in
 // registers for NU = 1; for NU = 2 the universes take them and W_m sits in LDS.
@@ -188,8 +158,8 @@ k_fixed_small(const FxTileDesc *__restrict__ tiles, int64_t n_tiles,
               const double *__restrict__ W64, const double *__restrict__ Xt,
               const double *__restrict__ Y, const double *__restrict__ a,
               const int64_t *__restrict__ p_of_row, int N, int64_t G, int64_t q_per_chunk,
-              int n_chunks, int stride, double *__restrict__ cand_v,
-              int64_t *__restrict__ cand_q, double *__restrict__ cp)
+              int n_chunks, double *__restrict__ cand_v, int64_t *__restrict__ cand_q,
+              double *__restrict__ cp)
 {
     constexpr int NP = 4 * NS, NC = (NP + 15) / 16;
     // steps of component block c: up to the diagonal
@@ -342,20 +312,22 @@ k_fixed_small(const FxTileDesc *__restrict__ tiles, int64_t n_tiles,
                 q = oq;
             }
         }
-        fixed_candidate(cand_v, cand_q, td.r0 + tid, stride, chunk, n_chunks, v, q);
+        const int64_t c = td.cand0 + (int64_t)tid * n_chunks + chunk;
+        cand_v[c] = v;
+        cand_q[c] = q;
     }
 }
 
-// Running minimum of one (tile, grid chunk): candidates cand_v/cand_q
-// [row][stride], chi2 at the true point into cp[row] (exactly one block
-// meets q == p for each row).
+// Running minimum of one (tile, grid chunk): the candidate of each of the tile's
+// rows, chi2 at the true point into cp[row] (exactly one block meets q == p for
+// each row).
 template <int NS>
 __global__ __launch_bounds__(kFxThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_fixed_min(
     const FxTileDesc *__restrict__ tiles, int64_t n_tiles, const double *__restrict__ Y,
     const double *__restrict__ a, const int64_t *__restrict__ p_of_row,
     const double *__restrict__ T, const double *__restrict__ b, int64_t b_stride, int64_t G,
-    int64_t q_per_chunk, int n_chunks, int stride, double *__restrict__ cand_v,
-    int64_t *__restrict__ cand_q, double *__restrict__ cp)
+    int64_t q_per_chunk, int n_chunks, double *__restrict__ cand_v, int64_t *__restrict__ cand_q,
+    double *__restrict__ cp)
 {
     constexpr int NP = 4 * NS;             // padded bins
     constexpr int TU = kFxTile * NP / 2;   // 16-byte units of a t tile (rows contiguous)
@@ -521,30 +493,56 @@ __global__ __launch_bounds__(kFxThreads) __attribute__((amdgpu_waves_per_eu(2)))
                 q = oq;
             }
         }
-        fixed_candidate(cand_v, cand_q, td.r0 + tid, stride, chunk, n_chunks, v, q);
+        const int64_t c = td.cand0 + (int64_t)tid * n_chunks + chunk;
+        cand_v[c] = v;
+        cand_q[c] = q;
     }
 }
 
-// Merge the chunks of row r and write the universe's outputs (original order).
+// Merge the chunks of each row and write the universe's outputs (original
+// order): one wave per tile, as many lanes a row as there are to spare.
+struct FxChunks {
+    int64_t tile_end[kFxLaunches];
+    int n_chunks[kFxLaunches];
+};
 __global__ __launch_bounds__(256) void k_fixed_finish(
-    int64_t R, int n_chunks, const double *__restrict__ cand_v,
-    const int64_t *__restrict__ cand_q, const double *__restrict__ cp,
-    const int64_t *__restrict__ order, const int64_t *__restrict__ p_of_row,
-    double *__restrict__ dchi2, double *__restrict__ chi2_min, int64_t *__restrict__ argmin,
-    double *__restrict__ chi2_p)
+    const FxTileDesc *__restrict__ tiles, int64_t n_tiles, FxChunks ch,
+    const double *__restrict__ cand_v, const int64_t *__restrict__ cand_q,
+    const double *__restrict__ cp, const int64_t *__restrict__ order,
+    const int64_t *__restrict__ p_of_row, double *__restrict__ dchi2,
+    double *__restrict__ chi2_min, int64_t *__restrict__ argmin, double *__restrict__ chi2_p)
 {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= R) return;
+    const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (t >= n_tiles) return;  // whole wave
+    const int lane = threadIdx.x & 63;
+    const FxTileDesc td = tiles[t];
+    int n_chunks = ch.n_chunks[kFxLaunches - 1];
+    for (int k = kFxLaunches - 2; k >= 0; --k)
+        if (t < ch.tile_end[k]) n_chunks = ch.n_chunks[k];
+    int share = 64;  // lanes a row
+    while (share * td.n > 64) share >>= 1;
+    const int row = lane / share;
+    const int64_t r = td.r0 + row;
     double v = __builtin_inf();
     int64_t q = INT64_MAX;
-    for (int c = 0; c < n_chunks; ++c) {
-        const double ov = cand_v[r * n_chunks + c];
-        const int64_t oq = cand_q[r * n_chunks + c];
+    if (row < td.n)
+        for (int c = lane % share; c < n_chunks; c += share) {
+            const double ov = cand_v[td.cand0 + (int64_t)row * n_chunks + c];
+            const int64_t oq = cand_q[td.cand0 + (int64_t)row * n_chunks + c];
+            if (ov < v || (ov == v && oq < q)) {
+                v = ov;
+                q = oq;
+            }
+        }
+    for (int sh = 1; sh < share; sh <<= 1) {
+        const double ov = __shfl_xor(v, sh);
+        const int64_t oq = __shfl_xor(q, sh);
         if (ov < v || (ov == v && oq < q)) {
             v = ov;
             q = oq;
         }
     }
+    if (row >= td.n || lane % share) return;
     const int64_t k = order[r];
     if (!(v < __builtin_inf())) q = p_of_row[r];  // no chi2 below +inf: Algorithm 1 keeps p
     dchi2[k] = cp[r] - v;
@@ -575,27 +573,11 @@ struct Buf {
     template <class T> T *as() const { return reinterpret_cast<T *>(p); }
 };
 
-// One kernel's tiles of a round and their grid chunks (whole steps of kFxTile
-// points).
-struct FxLaunch {
-    const FxTileDesc *tiles = nullptr;
-    int64_t n_tiles = 0, q_per_chunk = 0;
-    int n_chunks = 0;
-
-    void chunks(int64_t G, int slots)
-    {
-        const int64_t steps = (G + kFxTile - 1) / kFxTile;
-        const ScanGeometry sg = scan_geometry(n_tiles, n_tiles, steps, slots, steps, kPointsChunks);
-        q_per_chunk = sg.q_per_chunk * kFxTile;
-        n_chunks = (int)sg.n_qchunks;
-    }
-};
-
 // Device arrays of a round's rows.
 struct FxRows {
+    const FxTileDesc *tiles;
     const double *Y, *a;
     const int64_t *p;
-    int stride;
     double *cand_v;
     int64_t *cand_q;
     double *cp;
@@ -606,8 +588,8 @@ hipError_t launch_fixed_min_ns(const fc_grid *g, const FxLaunch &l, const FxRows
                                const double *T, const double *b, int64_t b_stride, hipStream_t st)
 {
     hipLaunchKernelGGL((k_fixed_min<NS>), dim3((unsigned)(l.n_tiles * l.n_chunks)),
-                       dim3(kFxThreads), 0, st, l.tiles, l.n_tiles, r.Y, r.a, r.p, T, b, b_stride,
-                       g->G, l.q_per_chunk, l.n_chunks, r.stride, r.cand_v, r.cand_q, r.cp);
+                       dim3(kFxThreads), 0, st, r.tiles + l.tile0, l.n_tiles, r.Y, r.a, r.p, T, b,
+                       b_stride, g->G, l.q_per_chunk, l.n_chunks, r.cand_v, r.cand_q, r.cp);
     return hipGetLastError();
 }
 
@@ -616,8 +598,8 @@ hipError_t launch_fixed_small_ns(const fc_grid *g, const FxLaunch &l, const FxRo
                                  const double *Xt, hipStream_t st)
 {
     hipLaunchKernelGGL((k_fixed_small<NS, NU>), dim3((unsigned)(l.n_tiles * l.n_chunks)),
-                       dim3(kFxThreads), 0, st, l.tiles, l.n_tiles, g->W64, Xt, r.Y, r.a, r.p, g->N,
-                       g->G, l.q_per_chunk, l.n_chunks, r.stride, r.cand_v, r.cand_q, r.cp);
+                       dim3(kFxThreads), 0, st, r.tiles + l.tile0, l.n_tiles, g->W64, Xt, r.Y, r.a,
+                       r.p, g->N, g->G, l.q_per_chunk, l.n_chunks, r.cand_v, r.cand_q, r.cp);
     return hipGetLastError();
 }
 
@@ -695,44 +677,13 @@ static hipError_t fixed_round(const fc_grid *g, int64_t R, const std::vector<int
     hipError_t e;
     int64_t r_begin = 0;
     while (r_begin < R) {
-        // rows r_begin .. r_end cover at most slots_max groups with a t table
-        std::vector<int64_t> slot_m;
-        // tiles of k_fixed_min, and of k_fixed_small with one and two blocks of 16
-        std::vector<FxTileDesc> tiles, small[2];
-        int64_t r = r_begin;
-        while (r < R) {
-            const int64_t m = h_m[r];
-            int64_t r2 = r;
-            while (r2 < R && h_m[r2] == m) ++r2;
-            const bool table = r2 - r > kFxSmall;
-            if (table && (int64_t)slot_m.size() == slots_max) break;
-            FxTileDesc td;
-            td.slot = table ? (int32_t)slot_m.size() : (int32_t)m;
-            if (table) slot_m.push_back(m);
-            for (int64_t t0 = r; t0 < r2; t0 += td.n) {
-                td.r0 = t0 - r_begin;
-                td.n = (int32_t)std::min<int64_t>(table ? kFxTile : 32, r2 - t0);
-                (table ? tiles : small[td.n > 16]).push_back(td);
-            }
-            r = r2;
-        }
-        const int64_t r_end = r, nr = r_end - r_begin, n_slots = (int64_t)slot_m.size();
         static const int slots_res =  // queried once (thread-safe); all three: two blocks a CU
             resident_slots(reinterpret_cast<const void *>(&k_fixed_min<15>), kFxThreads);
-        FxLaunch big, sm[2];
-        big.n_tiles = (int64_t)tiles.size();
-        for (int k = 0; k < 2; ++k) {
-            sm[k].n_tiles = (int64_t)small[k].size();
-            tiles.insert(tiles.end(), small[k].begin(), small[k].end());
-        }
-        const int64_t all = (int64_t)tiles.size();
-        FxRows rows;
-        rows.stride = 1;
-        for (FxLaunch *l : {&big, &sm[0], &sm[1]})
-            if (l->n_tiles) {
-                l->chunks(G, slots_res);
-                rows.stride = std::max(rows.stride, l->n_chunks);
-            }
+        const int resident[kFxLaunches] = {slots_res, slots_res, slots_res};
+        const FxBatch batch = fixed_batch(h_m.data(), r_begin, R, G, slots_max, resident);
+        const FxLaunch *const l = batch.launch;
+        const int64_t nr = batch.r_end - r_begin, n_slots = (int64_t)batch.slot_m.size();
+        const int64_t all = (int64_t)batch.tiles.size();
         const int64_t nx = (G + 15) / 16 * 64 * ns;  // elements of X
 
         if ((e = dOrder.need(sizeof(int64_t) * nr)) != hipSuccess ||
@@ -744,20 +695,19 @@ static hipError_t fixed_round(const fc_grid *g, int64_t R, const std::vector<int
             (n_slots && (e = dB.need(sizeof(double) * (size_t)n_slots * b_stride)) != hipSuccess) ||
             (n_slots && (e = dSlotM.need(sizeof(int64_t) * n_slots)) != hipSuccess) ||
             (e = dTiles.need(sizeof(FxTileDesc) * all)) != hipSuccess ||
-            (e = dCv.need(sizeof(double) * nr * rows.stride)) != hipSuccess ||
-            (e = dCq.need(sizeof(int64_t) * nr * rows.stride)) != hipSuccess ||
+            (e = dCv.need(sizeof(double) * batch.n_cand)) != hipSuccess ||
+            (e = dCq.need(sizeof(int64_t) * batch.n_cand)) != hipSuccess ||
             (e = dCp.need(sizeof(double) * nr)) != hipSuccess)
             return e;
-        big.tiles = dTiles.as<FxTileDesc>();
-        sm[0].tiles = big.tiles + big.n_tiles;
-        sm[1].tiles = sm[0].tiles + sm[0].n_tiles;
+        FxRows rows;
+        rows.tiles = dTiles.as<FxTileDesc>();
         rows.Y = dY.as<double>();
         rows.a = dA.as<double>();
         rows.p = dP.as<int64_t>();
         rows.cand_v = dCv.as<double>();
         rows.cand_q = dCq.as<int64_t>();
         rows.cp = dCp.as<double>();
-        if (sm[0].n_tiles + sm[1].n_tiles && !dX.p) {  // once per call
+        if (all > l[kFxTable].n_tiles && !dX.p) {  // once per call
             if ((e = dX.need(sizeof(double) * (size_t)nx)) != hipSuccess) return e;
             hipLaunchKernelGGL(k_fixed_x, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st,
                                g->S64, g->off, N, ns, G, nx, dX.as<double>());
@@ -769,9 +719,9 @@ static hipError_t fixed_round(const fc_grid *g, int64_t R, const std::vector<int
                                 hipMemcpyHostToDevice, st)) != hipSuccess ||
             (e = hipMemcpyAsync(dP.p, h_p.data() + r_begin, sizeof(int64_t) * nr,
                                 hipMemcpyHostToDevice, st)) != hipSuccess ||
-            (n_slots && (e = hipMemcpyAsync(dSlotM.p, slot_m.data(), sizeof(int64_t) * n_slots,
+            (n_slots && (e = hipMemcpyAsync(dSlotM.p, batch.slot_m.data(), sizeof(int64_t) * n_slots,
                                             hipMemcpyHostToDevice, st)) != hipSuccess) ||
-            (e = hipMemcpyAsync(dTiles.p, tiles.data(), sizeof(FxTileDesc) * all,
+            (e = hipMemcpyAsync(dTiles.p, batch.tiles.data(), sizeof(FxTileDesc) * all,
                                 hipMemcpyHostToDevice, st)) != hipSuccess)
             return e;
         // chi2 at the true point is always met (p is a grid point); NaN until then
@@ -779,24 +729,29 @@ static hipError_t fixed_round(const fc_grid *g, int64_t R, const std::vector<int
                            g->off, dOrder.as<int64_t>(), dM.as<int64_t>(), N, np, nr,
                            dY.as<double>(), dA.as<double>());
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (big.n_tiles &&
+        if (l[kFxTable].n_tiles &&
             ((e = launch_fixed_t(ns, g, dSlotM.as<int64_t>(), n_slots, b_stride, dT.as<double>(),
                                  dB.as<double>(), st)) != hipSuccess ||
-             (e = launch_fixed_min(ns, g, big, rows, dT.as<double>(), dB.as<double>(), b_stride,
-                                   st)) != hipSuccess))
+             (e = launch_fixed_min(ns, g, l[kFxTable], rows, dT.as<double>(), dB.as<double>(),
+                                   b_stride, st)) != hipSuccess))
             return e;
-        for (int k = 0; k < 2; ++k)
-            if (sm[k].n_tiles && (e = launch_fixed_small(ns, k + 1, g, sm[k], rows,
-                                                         dX.as<double>(), st)) != hipSuccess)
+        for (int k : {kFxSmall16, kFxSmall32})
+            if (l[k].n_tiles && (e = launch_fixed_small(ns, k == kFxSmall16 ? 1 : 2, g, l[k], rows,
+                                                        dX.as<double>(), st)) != hipSuccess)
                 return e;
-        hipLaunchKernelGGL(k_fixed_finish, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, st,
-                           nr, rows.stride, dCv.as<double>(), dCq.as<int64_t>(), dCp.as<double>(),
+        FxChunks ch;
+        for (int k = 0; k < kFxLaunches; ++k) {
+            ch.tile_end[k] = l[k].tile0 + l[k].n_tiles;
+            ch.n_chunks[k] = l[k].n_chunks;
+        }
+        hipLaunchKernelGGL(k_fixed_finish, dim3((unsigned)((all + 3) / 4)), dim3(256), 0, st,
+                           rows.tiles, all, ch, rows.cand_v, rows.cand_q, rows.cp,
                            dOrder.as<int64_t>(), dP.as<int64_t>(), dchi2, chi2_min, argmin,
                            chi2_p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         // the host vectors above are reused by the next batch
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-        r_begin = r_end;
+        r_begin = batch.r_end;
     }
     return hipSuccess;
 }
