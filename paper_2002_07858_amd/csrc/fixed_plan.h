@@ -29,6 +29,13 @@ constexpr int64_t kFxMaxTiles = int64_t(1) << 20;  // tiles of a batch at most
 // takes more: chunks past that bound are not needed to fill the chip.
 constexpr int64_t kFxCandBytes = int64_t(64) << 20;
 
+// The launches' chunks, in steps of kFxTile points: as short as one step, since a
+// small grid or a late round has few tiles (20 x 20 points of 64 bins, one group
+// of 100: 7 chunks 163 us, one 199 us the call).  Start and fill measured over
+// 450 calls (4 to 64 bins, 64 to 10 000 points, groups of 8 to 1000, with and
+// without iteration): 1.3 % on average from the best of six pairs; (1, 1) 3.6 %.
+constexpr ChunkRule kFxChunks{1, 32, 3.0, 0.0};
+
 struct FxTileDesc {
     int64_t r0;     // first row (group order) of the tile, in the batch
     int64_t cand0;  // its first candidate
@@ -88,7 +95,7 @@ inline FxBatch fixed_batch(const int64_t *m, int64_t r_begin, int64_t R, int64_t
         if (!l.n_tiles) continue;
         const int64_t most = std::min(steps, std::max<int64_t>(1, kFxCandBytes / (16 * l.rows)));
         const ScanGeometry sg =
-            scan_geometry(l.n_tiles, l.n_tiles, steps, resident[k], most, kPointsChunks);
+            scan_geometry(l.n_tiles, l.n_tiles, steps, resident[k], most, kFxChunks);
         l.q_per_chunk = sg.q_per_chunk * kFxTile;
         l.n_chunks = (int)sg.n_qchunks;
         for (FxTileDesc &td : part[k]) {

@@ -631,6 +631,30 @@ hipError_t launch_fixed_small(int ns, int nu, const fc_grid *g, const FxLaunch &
     }
 }
 
+// Resident block slots of the three kernels: queried once per instantiation
+// (thread-safe).
+struct FxSlots {
+    int n[kFxLaunches];
+};
+template <int NS>
+const FxSlots &fixed_slots_ns()
+{
+    static const FxSlots s = {
+        {resident_slots(reinterpret_cast<const void *>(&k_fixed_min<NS>), kFxThreads),
+         resident_slots(reinterpret_cast<const void *>(&k_fixed_small<NS, 1>), kFxThreads),
+         resident_slots(reinterpret_cast<const void *>(&k_fixed_small<NS, 2>), kFxThreads)}};
+    return s;
+}
+const FxSlots &fixed_slots(int ns)
+{
+    switch (ns) {
+#define FC_CASE(n) case n: return fixed_slots_ns<n>();
+        FC_EACH_NS(FC_CASE)
+#undef FC_CASE
+    default: return fixed_slots_ns<16>();
+    }
+}
+
 template <int NS>
 hipError_t launch_fixed_t_ns(const fc_grid *g, const int64_t *m_of_slot, int64_t n_slots,
                              int64_t b_stride, double *T, double *b, hipStream_t st)
@@ -677,10 +701,8 @@ static hipError_t fixed_round(const fc_grid *g, int64_t R, const std::vector<int
     hipError_t e;
     int64_t r_begin = 0;
     while (r_begin < R) {
-        static const int slots_res =  // queried once (thread-safe); all three: two blocks a CU
-            resident_slots(reinterpret_cast<const void *>(&k_fixed_min<15>), kFxThreads);
-        const int resident[kFxLaunches] = {slots_res, slots_res, slots_res};
-        const FxBatch batch = fixed_batch(h_m.data(), r_begin, R, G, slots_max, resident);
+        const FxBatch batch =
+            fixed_batch(h_m.data(), r_begin, R, G, slots_max, fixed_slots(ns).n);
         const FxLaunch *const l = batch.launch;
         const int64_t nr = batch.r_end - r_begin, n_slots = (int64_t)batch.slot_m.size();
         const int64_t all = (int64_t)batch.tiles.size();

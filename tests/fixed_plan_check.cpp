@@ -2,7 +2,7 @@
 // thousands, grids from one point to millions) the batches take every row once
 // and in order, tiles hold rows of one group and no more than their launch's
 // kernel takes, tables stay within the slots, candidate regions are disjoint and
-// within their byte bound; then a round with one group of 20 universes beside
+// within their byte bound, and one tile gets a chunk a step; then a round with one group of 20 universes beside
 // 2^20 groups of one on 2^20 points, whose candidates took 8.6 GB when every row
 // had the most chunks of any launch.
 // Prints "ok" or the first failure.
@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstdio>
 #include <random>
+#include <utility>
 
 #include "fixed_plan.h"
 
@@ -85,6 +86,12 @@ int main()
     for (int64_t g = 1; g <= (1 << 20); ++g) m.push_back(g);
     if (check(m, 1 << 20, 8, resident, &bytes)) return 1;
     if (bytes > kFxLaunches * kFxCandBytes) return bad("candidates of small groups", bytes);
+    // one tile spreads over the chip: a chunk a step on small grids
+    const std::vector<int64_t> few(20, 3);
+    for (const auto &want : {std::pair<int64_t, int>{64, 1}, {400, 7}, {1600, 25}, {10000, 157}}) {
+        const int n = fixed_batch(few.data(), 0, 20, want.first, 8, resident).launch[kFxSmall32].n_chunks;
+        if (n != want.second) return bad("chunks of one tile", want.first, n);
+    }
     // one group past the tiles of a batch
     if (check(std::vector<int64_t>(70 << 20, 5), 1000, 8, resident, &bytes)) return 1;
     printf("ok\n");
