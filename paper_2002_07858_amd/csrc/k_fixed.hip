@@ -25,7 +25,7 @@
 // registers; the t tile (64 points x 4*NS bins) is double-buffered in LDS and
 // brought in by direct global -> LDS loads while the previous tile is used.
 //
-// Groups of at most kFxSmall universes (almost all of them once the matrices
+// Groups of a few hundred universes at most (fixed_plan.h; almost all of them once the matrices
 // are those of the minimisers) would leave much of that tile empty and write
 // and read a whole t table for a few universes.  k_fixed_small forms t_q on
 // the fly instead: with W_m as the A operand, t^T = W_m X^T comes out of the
@@ -573,6 +573,24 @@ struct Buf {
     template <class T> T *as() const { return reinterpret_cast<T *>(p); }
 };
 
+// Device arrays of a batch, cut from one allocation: take() lays out, at() gives
+// the address once the buffer is there.  A small call's time is mostly its
+// allocations (100 universes x 400 points of 64 bins: 163 us with 13, 143 us
+// with four; one of more than 2 MiB takes 40 us more, so that y has its own).
+struct FxArrays {
+    size_t used = 0;
+    size_t take(size_t bytes)
+    {
+        const size_t at = used;
+        used += (bytes + 255) & ~size_t(255);
+        return at;
+    }
+    template <class T> static T *at(const Buf &b, size_t off)
+    {
+        return reinterpret_cast<T *>(static_cast<char *>(b.p) + off);
+    }
+};
+
 // Device arrays of a round's rows.
 struct FxRows {
     const FxTileDesc *tiles;
@@ -695,67 +713,65 @@ static hipError_t fixed_round(const fc_grid *g, int64_t R, const std::vector<int
     const size_t t_bytes_per_slot = sizeof(double) * ((size_t)G * np + b_stride);
     const size_t budget = size_t(4) << 30;
     const int64_t slots_max = std::max<int64_t>(1, (int64_t)(budget / t_bytes_per_slot));
-    Buf &dOrder = bufs[0], &dM = bufs[1], &dP = bufs[2], &dY = bufs[3], &dA = bufs[4],
-        &dT = bufs[5], &dB = bufs[6], &dSlotM = bufs[7], &dTiles = bufs[8], &dCv = bufs[9],
-        &dCq = bufs[10], &dCp = bufs[11], &dX = bufs[12];
+    Buf &dRows = bufs[0], &dY = bufs[1], &dT = bufs[2], &dX = bufs[3];
     hipError_t e;
     int64_t r_begin = 0;
     while (r_begin < R) {
         const FxBatch batch =
-            fixed_batch(h_m.data(), r_begin, R, G, slots_max, fixed_slots(ns).n);
+            fixed_batch(h_m.data(), r_begin, R, G, (int64_t)sizeof(double) * G * np, slots_max,
+                        fixed_slots(ns).n);
         const FxLaunch *const l = batch.launch;
         const int64_t nr = batch.r_end - r_begin, n_slots = (int64_t)batch.slot_m.size();
         const int64_t all = (int64_t)batch.tiles.size();
         const int64_t nx = (G + 15) / 16 * 64 * ns;  // elements of X
 
-        if ((e = dOrder.need(sizeof(int64_t) * nr)) != hipSuccess ||
-            (e = dM.need(sizeof(int64_t) * nr)) != hipSuccess ||
-            (e = dP.need(sizeof(int64_t) * nr)) != hipSuccess ||
+        FxArrays w;
+        const size_t order = w.take(sizeof(int64_t) * nr), m = w.take(sizeof(int64_t) * nr),
+                     p = w.take(sizeof(int64_t) * nr),
+                     a = w.take(sizeof(double) * nr), cp = w.take(sizeof(double) * nr),
+                     slot_m = w.take(sizeof(int64_t) * n_slots),
+                     tiles = w.take(sizeof(FxTileDesc) * all),
+                     cand_v = w.take(sizeof(double) * batch.n_cand),
+                     cand_q = w.take(sizeof(int64_t) * batch.n_cand);
+        FxArrays tab;
+        const size_t tt = tab.take(sizeof(double) * (size_t)n_slots * G * np),
+                     tb = tab.take(sizeof(double) * (size_t)n_slots * b_stride);
+        if ((e = dRows.need(w.used)) != hipSuccess ||
             (e = dY.need(sizeof(double) * nr * np)) != hipSuccess ||
-            (e = dA.need(sizeof(double) * nr)) != hipSuccess ||
-            (n_slots && (e = dT.need(sizeof(double) * (size_t)n_slots * G * np)) != hipSuccess) ||
-            (n_slots && (e = dB.need(sizeof(double) * (size_t)n_slots * b_stride)) != hipSuccess) ||
-            (n_slots && (e = dSlotM.need(sizeof(int64_t) * n_slots)) != hipSuccess) ||
-            (e = dTiles.need(sizeof(FxTileDesc) * all)) != hipSuccess ||
-            (e = dCv.need(sizeof(double) * batch.n_cand)) != hipSuccess ||
-            (e = dCq.need(sizeof(int64_t) * batch.n_cand)) != hipSuccess ||
-            (e = dCp.need(sizeof(double) * nr)) != hipSuccess)
+            (e = dT.need(tab.used)) != hipSuccess)
             return e;
-        FxRows rows;
-        rows.tiles = dTiles.as<FxTileDesc>();
-        rows.Y = dY.as<double>();
-        rows.a = dA.as<double>();
-        rows.p = dP.as<int64_t>();
-        rows.cand_v = dCv.as<double>();
-        rows.cand_q = dCq.as<int64_t>();
-        rows.cp = dCp.as<double>();
+        int64_t *const d_order = w.at<int64_t>(dRows, order), *const d_m = w.at<int64_t>(dRows, m),
+                      *const d_p = w.at<int64_t>(dRows, p),
+                      *const d_slot_m = w.at<int64_t>(dRows, slot_m);
+        FxTileDesc *const d_tiles = w.at<FxTileDesc>(dRows, tiles);
+        double *const Y = dY.as<double>(), *const ya = w.at<double>(dRows, a);
+        double *const T = tab.at<double>(dT, tt), *const b = tab.at<double>(dT, tb);
+        const FxRows rows{d_tiles, Y, ya, d_p, w.at<double>(dRows, cand_v),
+                          w.at<int64_t>(dRows, cand_q), w.at<double>(dRows, cp)};
         if (all > l[kFxTable].n_tiles && !dX.p) {  // once per call
             if ((e = dX.need(sizeof(double) * (size_t)nx)) != hipSuccess) return e;
             hipLaunchKernelGGL(k_fixed_x, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0, st,
                                g->S64, g->off, N, ns, G, nx, dX.as<double>());
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-        if ((e = hipMemcpyAsync(dOrder.p, h_order.data() + r_begin, sizeof(int64_t) * nr,
+        if ((e = hipMemcpyAsync(d_order, h_order.data() + r_begin, sizeof(int64_t) * nr,
                                 hipMemcpyHostToDevice, st)) != hipSuccess ||
-            (e = hipMemcpyAsync(dM.p, h_m.data() + r_begin, sizeof(int64_t) * nr,
+            (e = hipMemcpyAsync(d_m, h_m.data() + r_begin, sizeof(int64_t) * nr,
                                 hipMemcpyHostToDevice, st)) != hipSuccess ||
-            (e = hipMemcpyAsync(dP.p, h_p.data() + r_begin, sizeof(int64_t) * nr,
+            (e = hipMemcpyAsync(d_p, h_p.data() + r_begin, sizeof(int64_t) * nr,
                                 hipMemcpyHostToDevice, st)) != hipSuccess ||
-            (n_slots && (e = hipMemcpyAsync(dSlotM.p, batch.slot_m.data(), sizeof(int64_t) * n_slots,
+            (n_slots && (e = hipMemcpyAsync(d_slot_m, batch.slot_m.data(), sizeof(int64_t) * n_slots,
                                             hipMemcpyHostToDevice, st)) != hipSuccess) ||
-            (e = hipMemcpyAsync(dTiles.p, batch.tiles.data(), sizeof(FxTileDesc) * all,
+            (e = hipMemcpyAsync(d_tiles, batch.tiles.data(), sizeof(FxTileDesc) * all,
                                 hipMemcpyHostToDevice, st)) != hipSuccess)
             return e;
         // chi2 at the true point is always met (p is a grid point); NaN until then
         hipLaunchKernelGGL(k_fixed_y, dim3((unsigned)((nr + 3) / 4)), dim3(256), 0, st, g->W64, d,
-                           g->off, dOrder.as<int64_t>(), dM.as<int64_t>(), N, np, nr,
-                           dY.as<double>(), dA.as<double>());
+                           g->off, d_order, d_m, N, np, nr, Y, ya);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (l[kFxTable].n_tiles &&
-            ((e = launch_fixed_t(ns, g, dSlotM.as<int64_t>(), n_slots, b_stride, dT.as<double>(),
-                                 dB.as<double>(), st)) != hipSuccess ||
-             (e = launch_fixed_min(ns, g, l[kFxTable], rows, dT.as<double>(), dB.as<double>(),
-                                   b_stride, st)) != hipSuccess))
+            ((e = launch_fixed_t(ns, g, d_slot_m, n_slots, b_stride, T, b, st)) != hipSuccess ||
+             (e = launch_fixed_min(ns, g, l[kFxTable], rows, T, b, b_stride, st)) != hipSuccess))
             return e;
         for (int k : {kFxSmall16, kFxSmall32})
             if (l[k].n_tiles && (e = launch_fixed_small(ns, k == kFxSmall16 ? 1 : 2, g, l[k], rows,
@@ -768,8 +784,7 @@ static hipError_t fixed_round(const fc_grid *g, int64_t R, const std::vector<int
         }
         hipLaunchKernelGGL(k_fixed_finish, dim3((unsigned)((all + 3) / 4)), dim3(256), 0, st,
                            rows.tiles, all, ch, rows.cand_v, rows.cand_q, rows.cp,
-                           dOrder.as<int64_t>(), dP.as<int64_t>(), dchi2, chi2_min, argmin,
-                           chi2_p);
+                           d_order, d_p, dchi2, chi2_min, argmin, chi2_p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         // the host vectors above are reused by the next batch
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
@@ -792,7 +807,7 @@ hipError_t fixed_run(const fc_grid *g, int64_t K, const double *d, const int64_t
         return e;
     for (int64_t k = 0; k < K; ++k) m[k] = p[k];
     std::vector<char> active(K, 1);
-    Buf bufs[13];
+    Buf bufs[4];
     std::vector<int64_t> order, hm, hp, cnt;
     for (int round = 0;; ++round) {
         // counting sort of the active universes by m

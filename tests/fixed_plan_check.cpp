@@ -28,7 +28,7 @@ static int check(const std::vector<int64_t> &m, int64_t G, int64_t slots_max,
     const int64_t R = (int64_t)m.size();
     *cand_bytes = 0;
     for (int64_t r = 0; r < R;) {
-        const FxBatch b = fixed_batch(m.data(), r, R, G, slots_max, resident);
+        const FxBatch b = fixed_batch(m.data(), r, R, G, 32 * G, slots_max, resident);
         if (b.r_end <= r || b.r_end > R) return bad("batch end", r, b.r_end);
         if ((int64_t)b.slot_m.size() > slots_max) return bad("slots");
         if ((int64_t)b.tiles.size() > kFxMaxTiles) return bad("tiles");
@@ -89,9 +89,15 @@ int main()
     // one tile spreads over the chip: a chunk a step on small grids
     const std::vector<int64_t> few(20, 3);
     for (const auto &want : {std::pair<int64_t, int>{64, 1}, {400, 7}, {1600, 25}, {10000, 157}}) {
-        const int n = fixed_batch(few.data(), 0, 20, want.first, 8, resident).launch[kFxSmall32].n_chunks;
+        const int n = fixed_batch(few.data(), 0, 20, want.first, 512 * want.first, 8, resident).launch[kFxSmall32].n_chunks;
         if (n != want.second) return bad("chunks of one tile", want.first, n);
     }
+    // a group of 100: with a table where that is small, without where it is not
+    const std::vector<int64_t> hundred(100, 3);
+    for (const auto &want : {std::pair<int64_t, int64_t>{32 << 10, 2}, {33 << 10, 0}})
+        if (fixed_batch(hundred.data(), 0, 100, 400, want.first, 8, resident)
+                .launch[kFxTable].n_tiles != want.second)
+            return bad("table of", want.first);
     // one group past the tiles of a batch
     if (check(std::vector<int64_t>(70 << 20, 5), 1000, 8, resident, &bytes)) return 1;
     printf("ok\n");
