@@ -78,14 +78,14 @@ __global__ __launch_bounds__(256) void k_finalize(int64_t K, const int64_t *__re
 // ---------------------------------------------------------------------------
 // Resident block slots of a kernel on the current device: CUs x blocks per CU
 // from the occupancy calculator.
-int resident_slots(const void *kernel, int block_threads)
+int resident_slots(const void *kernel, int block_threads, size_t dynamic_lds)
 {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
         return 512;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block_threads, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block_threads, dynamic_lds) !=
             hipSuccess ||
         per_cu <= 0)
         per_cu = 2;

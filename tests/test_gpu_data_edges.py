@@ -48,3 +48,21 @@ def test_data_scan_leaves_the_pool_alone(fc):  # noqa: F811
     # a scan without outputs of its own does take pool memory
     assert pool_peak(lambda: fc.fc_scan(g, FORM["fp32"], dd, pp, dchi2)) > 0
     assert pool_peak(lambda: fc.fc_data_scan(g, out)) == 0
+
+
+# the largest bin count's triangles take more than 64 KiB of LDS a block; grids
+# of one point, of a block's points and around them, and of several rounds of
+# resident blocks
+@pytest.mark.parametrize("N", [1, 2, 33, 57, 63, 64])
+@pytest.mark.parametrize("G", [1, 3, 4, 5, 9001])
+def test_data_scan_sizes(fc, N, G):  # noqa: F811
+    S, F, _, d = small_problem(N, G, 1, 2)
+    g = fc.fc_build_grid([np.arange(G, dtype=float)], S, d[0])
+    fc.fc_build_covariance(g, F, forms=FORM["fp64"])
+    out = torch.full((G,), -7.0, dtype=torch.float64, device="cuda")
+    low, at = fc.fc_data_scan(g, out)
+    ref, rlow, rat = oracle.data_scan(S, F, d[0])
+    scale = np.maximum(1.0, ref + rlow)
+    assert np.all(np.abs(out.cpu().numpy() - ref) <= parity.TOL["fp64"] * scale)
+    assert abs(low - rlow) <= parity.TOL["fp64"] * max(1.0, rlow)
+    assert ref[at] <= 2 * parity.TOL["fp64"] * max(1.0, rlow)
