@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -380,13 +381,19 @@ inline void cov_map_fp64(int N, int16_t *m)
     const int n = 2 * f64_rec_units(N), nt = f64_ntile(N), P = f64_pad(N), nbe = f64_nbe(N);
     const int nb = f64_nb(N), sig = f64_sig_double(N), lead = f64_lead_double(N);
     const int nl = f64_lead(N);
+    // the tiles in order (f64_tile_at walks them anew for each)
+    std::vector<F64Tile> tile;
+    for (int g = 0; g < f64_ngroup(N); ++g) {
+        const int r0 = f64_group_r0(N, g), r1 = f64_group_r0(N, g + 1);
+        for (int kb = f64_k0(N); kb < r1; ++kb)
+            for (int r = kb > r0 ? kb : r0; r < r1; ++r) tile.push_back(F64Tile{g, kb, r});
+    }
     for (int e = 0; e < n; ++e) {
         int16_t v = kMapZero;
         if (e < sig) {
             const int t = 2 * (e >> 5) + (e & 1), pos = (e >> 1) & 15;
             if (t < nt)
-                v = map_w(N, 4 * f64_tile_r(N, t) + (pos & 3) - P,
-                          4 * f64_tile_kb(N, t) + (pos >> 2) - P);
+                v = map_w(N, 4 * tile[t].r + (pos & 3) - P, 4 * tile[t].kb + (pos >> 2) - P);
         } else if (e < lead) {
             const int g = (e - sig) / nbe, r = (e - sig) % nbe, k = 4 * r + g - P;
             if (k >= 0 && k < N) v = (int16_t)(kMapSig + k);
@@ -402,16 +409,18 @@ inline void cov_map_fp64(int N, int16_t *m)
 // A[v/4][lane][v%4] with lane 4 X + m holding the pair at position 16 v + X.
 inline void cov_map_fp32(int ns, int N, int16_t *m)
 {
-    const int P = fp32_pad(ns, N), np = fp32_npairs(ns);
-    for (int v = 0; v < 4 * n_groups_from_ns(ns); ++v)
-        for (int lane = 0; lane < 64; ++lane) {
-            const int i = 16 * v + (lane >> 2), mm = lane & 3;
-            int16_t x = kMapZero;
-            const int t = fp32_pair_at(ns, i);
-            if (t < np)
-                x = map_w(N, 4 * fp32_pair_b(ns, t) + mm - P, fp32_pair_kp(ns, t) - P);
-            m[((v >> 2) * 64 + lane) * 4 + (v & 3)] = x;
-        }
+    const int P = fp32_pad(ns, N);
+    std::fill(m, m + 4 * rec_w_units(ns), kMapZero);
+    int i = 0;  // the pairs in order (fp32_pair_at walks them anew for each)
+    for (int g = 0; g < fp32_ngroup(ns); ++g) {
+        const int b0 = fp32_group_b0(ns, g), b1 = fp32_group_b0(ns, g + 1);
+        for (int kp = 0; kp < 4 * b1; ++kp)
+            for (int b = kp / 4 > b0 ? kp / 4 : b0; b < b1; ++b, ++i)
+                for (int mm = 0; mm < 4; ++mm) {
+                    const int v = i / 16, lane = 4 * (i % 16) + mm;
+                    m[((v >> 2) * 64 + lane) * 4 + (v & 3)] = map_w(N, 4 * b + mm - P, kp - P);
+                }
+    }
 }
 
 // Split records, their fragments: eight entries per (fragment, lane), entry
