@@ -55,7 +55,7 @@ __global__ __launch_bounds__(T) void k_crit(const int64_t *__restrict__ seg_lo,
                                             int64_t *__restrict__ hist)
 {
     constexpr int BINS = 1 << BITS, NW = T / 64;
-    static_assert(BINS % 64 == 0 && kMaxAlpha * BINS * 4 >= kMaxAlpha * kCand * 8, "LDS sharing");
+    static_assert(T % kCand == 0 && BINS % 64 == 0 && kMaxAlpha * BINS * 4 >= kMaxAlpha * kCand * 8, "LDS sharing");
     // counters of every rank's interval, then its remaining keys
     __shared__ union {
         unsigned int cnt[kMaxAlpha][BINS];
@@ -201,19 +201,25 @@ __global__ __launch_bounds__(T) void k_crit(const int64_t *__restrict__ seg_lo,
         }
     }
     __syncthreads();
-    // keys below `own` among the first n of a list, equal ones by position
+    // keys below list[i] among its first n, equal ones by position; SUB lanes
+    // share a key's comparisons, so that a wide block is not mostly idle
+    constexpr int SUB = T / kCand;
     const auto below = [&](const unsigned long long *list, int n, int i) {
         const unsigned long long own = list[i];
         int b = 0;
 #pragma unroll 8
-        for (int c = 0; c < n; ++c) b += (list[c] < own || (list[c] == own && c < i)) ? 1 : 0;
+        for (int c = tid % SUB; c < n; c += SUB)
+            b += (list[c] < own || (list[c] == own && c < i)) ? 1 : 0;
+#pragma unroll
+        for (int m = 1; m < SUB; m <<= 1) b += __shfl_xor(b, m);
         return b;
     };
     if (K <= kCand) {
         // every key's rank, once for all alphas
         each([&](unsigned long long k) { sh.cand[0][atomicAdd(&fill_s[0], 1u)] = k; });
         __syncthreads();
-        for (int i = tid; i < (int)K; i += T) {
+        const int i = tid / SUB;
+        if (i < (int)K) {
             const int r = below(sh.cand[0], (int)K, i);
             for (int a = 0; a < n_alpha; ++a)
                 if (r == (int)rank_s[a])
@@ -231,29 +237,35 @@ __global__ __launch_bounds__(T) void k_crit(const int64_t *__restrict__ seg_lo,
         }
     });
     __syncthreads();
-    for (int e = tid; e < n_alpha * kCand; e += T) {
-        const int a = e / kCand, i = e % kCand, n = (int)fill_s[a];
-        if (shift_s[a] == 0) {
-            if (i == 0) crit[sgi * n_alpha + a] = from_order_key(lo_s[a]);
-        } else if (i < n) {
-            if (below(sh.cand[a], n, i) == (int)rank_s[a])
-                crit[sgi * n_alpha + a] = from_order_key(sh.cand[a][i]);
-        }
+    if (tid < n_alpha && shift_s[tid] == 0) crit[sgi * n_alpha + tid] = from_order_key(lo_s[tid]);
+    // (the intervals' keys one after the other: at a time they are few for the block)
+    for (int e = tid / SUB;; e += kCand) {
+        int a = 0, i = e;
+        while (a < n_alpha && i >= (int)fill_s[a]) i -= (int)fill_s[a++];
+        if (a == n_alpha) break;
+        if (below(sh.cand[a], (int)fill_s[a], i) == (int)rank_s[a])
+            crit[sgi * n_alpha + a] = from_order_key(sh.cand[a][i]);
     }
 }
 
 namespace {
 
-// Few segments: 1024 threads each, since a block's own latency is the time;
-// many: 256, so that several share a CU (1600 segments of 128-2048 values).
+// Up to a segment a CU: 1024 threads each, since a block's own latency is the
+// time; up to two, 512, so that both are resident; more, 256, so that several
+// share a CU.  300 segments of 300 / 2000 / 20 000 values: 1024 threads 20 / 21 /
+// 57 us, 512 10 / 13 / 58, 256 11 / 13 / 183; 256 segments of 20 000: 1024 threads
+// 31 us, 256 166; 1600 of 2048: 1024 threads 70 us, 256 19.
 hipError_t launch_crit_any(int64_t n_seg, const int64_t *seg_lo, const int64_t *seg_hi,
                            const double *x, int n_alpha, const AlphaArgs &aa,
                            const int64_t *ranks, double *crit, int n_bins, double hist_hi,
                            int64_t *hist, hipStream_t st)
 {
     const size_t lds = hist ? sizeof(unsigned int) * (size_t)(n_bins + 1) : 0;
-    if (n_seg <= 512)
+    if (n_seg <= 256)
         hipLaunchKernelGGL((k_crit<1024, 10, 20>), dim3((unsigned)n_seg), dim3(1024), lds, st,
+                           seg_lo, seg_hi, x, n_alpha, aa, ranks, crit, n_bins, hist_hi, hist);
+    else if (n_seg <= 512)
+        hipLaunchKernelGGL((k_crit<512, 10, 20>), dim3((unsigned)n_seg), dim3(512), lds, st,
                            seg_lo, seg_hi, x, n_alpha, aa, ranks, crit, n_bins, hist_hi, hist);
     else
         hipLaunchKernelGGL((k_crit<256, 9, 10>), dim3((unsigned)n_seg), dim3(256), lds, st, seg_lo,
