@@ -22,17 +22,21 @@
 // cos(2 pi u1) from words 0 and 1 of the bin's normal block.  A mean that is
 // negative, NaN or infinite gives count -1 and d = NaN.
 //
-// A block takes kGenRows universes at a time, one thread per (universe, bin).
+// A block takes a tile of up to kGenRows universes, one thread per (universe, bin).
 // Most Poisson draws end at the first attempt's squeeze; with a lane per bin of
 // one universe, some lane of every wave needed the exact test (two logarithms
 // and lgamma) and the whole wave waited through it up to four times.  The draws
 // that the squeeze does not settle therefore go to a list in LDS and are drawn
-// afterwards with full waves.  The constants of the squeeze depend on (p, bin)
-// alone and are tabulated per block while consecutive universes share p; L_F
+// afterwards with full waves; a tile with at most one draw a thread has nothing
+// to gain from that and draws at once.  The constants of the squeeze depend on
+// (p, bin) alone and are tabulated where a tile has one point; L_F
 // sits in LDS by columns (consecutive bins, consecutive addresses).  Bound:
 // FP64 and 64-bit integer vector arithmetic (two Philox blocks of 20 64 x 64
 // products each).  16 x 10 000 universes, N = 57: 1.12 ms with one wave per
-// universe, 0.47 ms so.
+// universe, 0.47 ms so.  Short segments, one universe each of 400 / 4000 / 40 000
+// points, N = 57, stream of calls: 16.8 / 37.5 / 319 us with one wave per
+// universe, 19.5 / 43.7 / 203 through a table of the tile's first point alone,
+// 15.0 / 32.4 / 170 so.
 //
 // The arithmetic is FP64 without contraction, in the order written, so the
 // counts are the same integers on any IEEE machine that evaluates
@@ -208,31 +212,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     __shared__ double lft[kMaxBins * kMaxBins];  // L_F by columns: lft[l N + i]
     __shared__ double gs[kGenRows][kMaxBins];    // normals
     __shared__ int64_t ns[kGenRows][kMaxBins];   // counts
-    __shared__ Ptrs cs[kMaxBins];                // squeeze constants of point p_cs
+    __shared__ Ptrs cs[kMaxBins];                // squeeze constants of a tile's one point
     __shared__ double lam_s[kMaxBins];           // its means
     __shared__ int64_t pk_s[kGenRows], j_s[kGenRows];
     __shared__ uint16_t slow[kGenRows * kMaxBins];  // draws the squeeze left open
-    __shared__ int n_slow;
+    __shared__ int n_slow, one_s;
     const int tid = threadIdx.x;
-    for (int e = tid; e < N * N; e += 256) lft[(e % N) * N + e / N] = LF[e];
     const int64_t r0 = row0 + (int64_t)blockIdx.x * tile_rows;
     if (r0 >= K) return;
     const int rows = (int)(K - r0 < tile_rows ? K - r0 : tile_rows);
-    if (tid < rows) {
-        const int64_t k = segment_of(seg_off, n_pts, r0 + tid);
-        const int64_t pk = p[k];
-        pk_s[tid] = (pk >= 0 && pk < G) ? pk : -1;
-        j_s[tid] = (u_first ? u_first[k] : 0) + (r0 + tid - seg_off[k]);
-        if (p_idx) p_idx[r0 + tid] = pk_s[tid];
+    if (tid < 64) {  // one wave looks up the rows while the others bring L_F
+        int64_t pk = -1;
+        if (tid < rows) {
+            const int64_t k = segment_of(seg_off, n_pts, r0 + tid);
+            pk = p[k];
+            pk = (pk >= 0 && pk < G) ? pk : -1;
+            pk_s[tid] = pk;
+            j_s[tid] = (u_first ? u_first[k] : 0) + (r0 + tid - seg_off[k]);
+            if (p_idx) p_idx[r0 + tid] = pk;
+        }
+        const int64_t first = __shfl(pk, 0);
+        const bool same = __all(tid >= rows || pk == first);
+        if (tid == 0) {
+            one_s = same;
+            n_slow = 0;
+        }
+    } else {
+        for (int e = tid - 64; e < N * N; e += 192) lft[(e % N) * N + e / N] = LF[e];
     }
-    if (tid == 0) n_slow = 0;
     __syncthreads();
-    const int64_t p_cs = pk_s[0];  // the point whose constants are tabulated
-    if (tid < N && p_cs >= 0) {
-        lam_s[tid] = S64[p_cs * N + tid];
-        cs[tid] = ptrs_constants(lam_s[tid]);
+    // the list pays where there are more draws than threads; else all draws are
+    // left open.  A tile of one point takes the squeeze's constants from a table,
+    // in one of several (short segments) each draw forms its own.
+    const bool squeeze = rows * N > 256, one = squeeze && one_s;  // uniform
+    if (one) {
+        const int64_t p_cs = pk_s[0];
+        if (tid < N && p_cs >= 0) {
+            lam_s[tid] = S64[p_cs * N + tid];
+            cs[tid] = ptrs_constants(lam_s[tid]);
+        }
+        __syncthreads();
     }
-    __syncthreads();
     // normals, and the counts that the first attempt's squeeze settles
     for (int e = tid; e < rows * N; e += 256) {
         const int u = e / N, i = e - u * N;
@@ -241,26 +261,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         int64_t n = -1;
         if (pk >= 0) {
             g = normal_draw(seed, pk, j, i);
-            bool open = true;
-            if (pk == p_cs && lam_s[i] >= 10.0 && !__builtin_isinf(lam_s[i])) {
-                uint64_t w[4];
-                stream_block(seed, pk, j, i, 0, 0, w);
-                double us, V;
-                const double kf = ptrs_candidate(cs[i], lam_s[i], w[0], w[1], us, V);
-                if (ptrs_squeeze(cs[i], us, V)) {
-                    n = (int64_t)kf;
-                    open = false;
+            if (squeeze) {
+                const double lam = one ? lam_s[i] : S64[pk * N + i];
+                if (lam >= 10.0 && !__builtin_isinf(lam)) {
+                    const Ptrs c = one ? cs[i] : ptrs_constants(lam);
+                    uint64_t w[4];
+                    stream_block(seed, pk, j, i, 0, 0, w);
+                    double us, V;
+                    const double kf = ptrs_candidate(c, lam, w[0], w[1], us, V);
+                    if (ptrs_squeeze(c, us, V)) n = (int64_t)kf;
                 }
+                if (n < 0) slow[atomicAdd(&n_slow, 1)] = (uint16_t)(u * kMaxBins + i);
             }
-            if (open) slow[atomicAdd(&n_slow, 1)] = (uint16_t)(u * kMaxBins + i);
         }
         gs[u][i] = g;
         ns[u][i] = n;
     }
     __syncthreads();
-    for (int e = tid; e < n_slow; e += 256) {
-        const int u = slow[e] / kMaxBins, i = slow[e] % kMaxBins;
-        ns[u][i] = poisson_draw(S64[pk_s[u] * N + i], seed, pk_s[u], j_s[u], i);
+    for (int e = tid; e < (squeeze ? n_slow : rows * N); e += 256) {
+        const int u = squeeze ? slow[e] / kMaxBins : e / N;
+        const int i = squeeze ? slow[e] % kMaxBins : e % N;
+        if (pk_s[u] >= 0)
+            ns[u][i] = poisson_draw(S64[pk_s[u] * N + i], seed, pk_s[u], j_s[u], i);
     }
     __syncthreads();
     // z_i = sum_{l <= i} L_F[i][l] g_l, increasing l
@@ -270,7 +292,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 #pragma unroll 8
         for (int l = 0; l < N; ++l) z = z + lft[l * N + i] * gs[u][l];  // L_F is 0 past i
         const int64_t pk = pk_s[u], n = ns[u][i];
-        const double lam = pk < 0 ? 0.0 : (pk == p_cs ? lam_s[i] : S64[pk * N + i]);
+        const double lam = pk < 0 ? 0.0 : (one ? lam_s[i] : S64[pk * N + i]);
         d[(r0 + u) * N + i] = (n < 0) ? __builtin_nan("") : (double)n + lam * z;
         if (counts) counts[(r0 + u) * N + i] = (int32_t)n;
     }
@@ -287,11 +309,12 @@ hipError_t launch_gen_universes(const fc_grid *g, int64_t n_pts, const int64_t *
                                 int64_t K, double *d, int64_t *p_idx, int32_t *counts,
                                 hipStream_t st)
 {
-    // few universes: smaller tiles, down to one bin a thread, on more CUs
+    // few universes: as small tiles as one round of resident blocks takes (4000,
+    // one a point, N = 57: tiles of 5 in 1.04 rounds 41 us, of 6 in 0.87 32 us)
     static const int slots =  // queried once (thread-safe)
         resident_slots(reinterpret_cast<const void *>(&k_gen_universes), 256);
-    const int64_t share = K / slots < kGenRows ? K / slots : kGenRows;
-    const int rows = share > 4 ? (int)share : 4;
+    const int64_t share = (K + slots - 1) / slots;
+    const int rows = share < kGenRows ? (int)share : kGenRows;
     const int64_t per_launch = (int64_t(1) << 22) * rows;  // blocks x 256 inside 32 bits
     for (int64_t row0 = 0; row0 < K; row0 += per_launch) {
         const int64_t n = K - row0 < per_launch ? K - row0 : per_launch;
