@@ -91,25 +91,28 @@ WORKLOADS = {
 # (the profiles directory holds the summaries).  Valid only while the kernel's
 # sources hash to the value the counters were taken with.
 FP32_SOURCES = tuple("paper_2002_07858_amd/csrc/" + f for f in
-                     ("k_scan_fp32.h", "k_scan.hip", "k_scan_pts.hip", "fc_internal.h"))
+                     ("k_scan_fp32.h", "k_scan.hip", "k_scan_pts.hip", "fc_internal.h",
+                      "scan_geometry.h"))
 SPLIT_SOURCES = ("paper_2002_07858_amd/csrc/k_scan_split.hip",
-                 "paper_2002_07858_amd/csrc/fc_internal.h")
+                 "paper_2002_07858_amd/csrc/fc_internal.h",
+                 "paper_2002_07858_amd/csrc/scan_geometry.h")
 FP64_SOURCES = ("paper_2002_07858_amd/csrc/k_scan64.hip",
-                "paper_2002_07858_amd/csrc/fc_internal.h")
+                "paper_2002_07858_amd/csrc/fc_internal.h",
+                "paper_2002_07858_amd/csrc/scan_geometry.h")
 # FETCH_SIZE (KiB x 1024 x 2.0000) + WRITE_SIZE (KiB x 1024 x 1.0000) of one launch
 # (a leg's: mean of the three launches of one run)
 TRAFFIC = {
-    ("c5", "fp64", "points"): {"bytes_per_launch": 413668829 * 2048 + 2781250 * 1024,
-                               "source_hash": "89f6d98ab5b6b439", "sources": FP64_SOURCES,
+    ("c5", "fp64", "points"): {"bytes_per_launch": 403635413 * 2048 + 2606250 * 1024,
+                               "source_hash": "c406df0b45783586", "sources": FP64_SOURCES,
                                "profile": "profiles/c5_all_forms.md"},
-    ("c5", "fp32", "points"): {"bytes_per_launch": 135335341 * 2048 + 641250 * 1024,
-                               "source_hash": "0bc2e426ebb2b1ce", "sources": FP32_SOURCES,
+    ("c5", "fp32", "points"): {"bytes_per_launch": 135338415 * 2048 + 641250 * 1024,
+                               "source_hash": "e71eb811567acd9c", "sources": FP32_SOURCES,
                                "profile": "profiles/c5_all_forms.md"},
-    ("c5", "split_fp16", "points"): {"bytes_per_launch": 2072373524 * 2048 + 2561250 * 1024,
-                                     "source_hash": "05fc610e0c577218", "sources": SPLIT_SOURCES,
+    ("c5", "split_fp16", "points"): {"bytes_per_launch": 2114617807 * 2048 + 2561250 * 1024,
+                                     "source_hash": "fb24f893ecc32653", "sources": SPLIT_SOURCES,
                                      "profile": "profiles/c5_all_forms.md"},
-    ("c5", "split_bf16", "points"): {"bytes_per_launch": 561525370 * 2048 + 6721251 * 1024,
-                                     "source_hash": "05fc610e0c577218", "sources": SPLIT_SOURCES,
+    ("c5", "split_bf16", "points"): {"bytes_per_launch": 551871122 * 2048 + 6721251 * 1024,
+                                     "source_hash": "fb24f893ecc32653", "sources": SPLIT_SOURCES,
                                      "profile": "profiles/c5_all_forms.md"},
 }
 

@@ -111,6 +111,11 @@ int fc_build_grid(fc_grid **out, int32_t D, const int64_t *axis_len,
  *   forms      non-empty OR of fc_form values
  *   bad_q      host out: first q whose Sigma_q is not positive definite, or -1
  *   stream     the call synchronises this stream before returning
+ * The grid keeps the device buffers of its forms and a small workspace (all in
+ * fc_grid_device_bytes) until it is destroyed or a build fails: a rebuild uses
+ * those of the forms it builds again and frees the others.  A rebuild therefore
+ * waits for all work on the current device first, on every stream and grid
+ * (hipDeviceSynchronize), since any of it may still read the old factors.
  * Returns FC_ERR_NOT_PD (with *bad_q set, no forms kept) if some Sigma_q has a
  * pivot <= 0 (or NaN) during the factorisation.
  */
