@@ -34,9 +34,12 @@
 // Measured at N = 57, 216 000 points: FP64 and FP32 forms (7.8 GB written, 1.6 ms
 // at the rate of a large copy) 6.87 ms with a lane per row and one column at a
 // time (every column read back through LDS as broadcasts, the LDS 60 % and the
-// vector units 47 % busy), 3.63 ms so; split FP16 form 7.40 and 4.15 ms.  What is
-// left is the chain of pivots (57 reciprocal roots, each after the last panel's
-// update) at two waves a SIMD, which the matrix tiles' registers allow.
+// vector units 47 % busy), 3.63 ms so; split FP16 form 7.40 and 4.15 ms.  The
+// bytes do not bound it (a third of them, FP32 records alone, takes 4 % less
+// time), nor the matrix cores (23 % busy): of the waves' time 39 % is waiting to
+// issue and 25 % for LDS or memory, at the two waves a SIMD that the matrix tiles'
+// registers allow, with vector instructions on 35 % of the cycles; the pivots'
+// reciprocal roots (57, each after the last panel's update) are one serial chain.
 #pragma once
 #include <stdint.h>
 

@@ -66,7 +66,7 @@ inline double scan_cost(int64_t tiles, int64_t G, int slots, const ChunkRule &ru
 // resident blocks, at most max_chunks chunks: the count of the least scan_cost.
 // All blocks of a launch take about the same time, one chunk each, so a round
 // that is not full is lost (FP64, 1000 tiles x 10 000 points on 768 slots: 5
-// chunks in 6.5 rounds 67.6 ms, 23 in 29.95 rounds 65.2 ms; split FP16, 20 tiles
+// chunks in 6.5 rounds 67.6 ms, 13 in 16.9 rounds 64.5 ms; split FP16, 20 tiles
 // x 216 000 points on 512 slots: 106 chunks in 4.1 rounds 12.7 ms, 128 in 5.0
 // rounds 11.0 ms).  The best count is an end of the range or the most chunks
 // that j blocks a CU hold, and what a last round loses matters little once j is
@@ -110,7 +110,7 @@ inline ScanGeometry scan_geometry(int64_t n_utiles, int64_t tiles, int64_t G, in
 // (k_scan_pts.hip) and an XCD's blocks stay there, so that a launch lasts as long
 // as its fullest XCD: the tiles that eight of those would hold (60 tiles: 64; 20
 // x 700 universes x 2500 points of 57 bins in 17 chunks on 1024 slots, 136 blocks
-// for an XCD's 128 slots, 1.32 ms, in 16 chunks 1.23 ms).
+// for an XCD's 128 slots, 1.32 ms, in 16 chunks 1.17 ms).
 inline int64_t pts_busy_tiles(int64_t tiles)
 {
     if (tiles <= 0) return 0;
