@@ -29,20 +29,22 @@
 // that the squeeze does not settle therefore go to a list in LDS and are drawn
 // afterwards with full waves; a tile with at most one draw a thread has nothing
 // to gain from that and draws at once.  The constants of the squeeze depend on
-// (p, bin) alone and are tabulated where a tile has one point; L_F
-// sits in LDS by columns (consecutive bins, consecutive addresses).  Bound:
-// FP64 and 64-bit integer vector arithmetic (two Philox blocks of 20 64 x 64
-// products each).  16 x 10 000 universes, N = 57: 1.12 ms with one wave per
+// (p, bin) alone and are tabulated for a tile's first point where segments are
+// long; L_F sits in LDS by columns (consecutive bins, consecutive addresses).
+// Bound: FP64 and 64-bit integer vector arithmetic (two Philox blocks of 20
+// 64 x 64 products each).  16 x 10 000 universes, N = 57: 1.12 ms with one wave per
 // universe, 0.47 ms so.  Short segments, one universe each of 400 / 4000 / 40 000
 // points, N = 57, stream of calls: 16.8 / 37.5 / 319 us with one wave per
 // universe, 19.5 / 43.7 / 203 through a table of the tile's first point alone,
-// 15.0 / 32.4 / 170 so.
+// 14.2 / 32.9 / 171 so.
 //
 // The arithmetic is FP64 without contraction, in the order written, so the
 // counts are the same integers on any IEEE machine that evaluates
 // exp/log/lgamma to within an ulp (a decision flips only if a uniform lands
 // within rounding of a boundary).
 #include "fc_internal.h"
+
+#include <algorithm>
 
 namespace fcx {
 
@@ -107,7 +109,7 @@ __device__ __forceinline__ bool ptrs_squeeze(const Ptrs &c, double us, double V)
 }
 
 // Poisson count for bin i of universe j at point p (-1: no valid mean).
-__device__ int64_t poisson_draw(double lam, uint64_t seed, int64_t p, int64_t j, int i)
+__device__ __forceinline__ int64_t poisson_draw(double lam, uint64_t seed, int64_t p, int64_t j, int i)
 {
     if (!(lam >= 0.0) || __builtin_isinf(lam)) return -1;
     if (lam == 0.0) return 0;
@@ -200,9 +202,15 @@ __device__ __forceinline__ int64_t segment_of(const int64_t *__restrict__ seg_of
 
 constexpr int kGenRows = 16;  // universes of a block at most
 
+// How a tile's Poisson draws go: all at once (at most a draw a thread), or the
+// squeeze first and the list then, with the constants of the tile's first point
+// from a table (draws of another point go to the list) or each draw's own.
+enum GenMode { kGenAtOnce, kGenTable, kGenOwn };
+
 // One tile of at most kGenRows universes a block (a loop over tiles lets the
 // compiler keep the library functions' constants in registers across it: 555
 // us at three waves per SIMD with spills, against 466).
+template <GenMode MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gen_universes(
     const double *__restrict__ S64, const double *__restrict__ LF, int N, int64_t G,
     int64_t n_pts, const int64_t *__restrict__ p, const int64_t *__restrict__ seg_off,
@@ -212,41 +220,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     __shared__ double lft[kMaxBins * kMaxBins];  // L_F by columns: lft[l N + i]
     __shared__ double gs[kGenRows][kMaxBins];    // normals
     __shared__ int64_t ns[kGenRows][kMaxBins];   // counts
-    __shared__ Ptrs cs[kMaxBins];                // squeeze constants of a tile's one point
+    __shared__ Ptrs cs[kMaxBins];                // squeeze constants of point p_cs
     __shared__ double lam_s[kMaxBins];           // its means
     __shared__ int64_t pk_s[kGenRows], j_s[kGenRows];
     __shared__ uint16_t slow[kGenRows * kMaxBins];  // draws the squeeze left open
-    __shared__ int n_slow, one_s;
+    __shared__ int n_slow;
     const int tid = threadIdx.x;
     const int64_t r0 = row0 + (int64_t)blockIdx.x * tile_rows;
     if (r0 >= K) return;
     const int rows = (int)(K - r0 < tile_rows ? K - r0 : tile_rows);
-    if (tid < 64) {  // one wave looks up the rows while the others bring L_F
-        int64_t pk = -1;
-        if (tid < rows) {
-            const int64_t k = segment_of(seg_off, n_pts, r0 + tid);
-            pk = p[k];
-            pk = (pk >= 0 && pk < G) ? pk : -1;
-            pk_s[tid] = pk;
-            j_s[tid] = (u_first ? u_first[k] : 0) + (r0 + tid - seg_off[k]);
-            if (p_idx) p_idx[r0 + tid] = pk;
-        }
-        const int64_t first = __shfl(pk, 0);
-        const bool same = __all(tid >= rows || pk == first);
-        if (tid == 0) {
-            one_s = same;
-            n_slow = 0;
-        }
-    } else {
-        for (int e = tid - 64; e < N * N; e += 192) lft[(e % N) * N + e / N] = LF[e];
+    // L_F by all threads, or where a call is few tiles and its time a tile's, by
+    // three waves while the first looks up the rows
+    constexpr int kLook = MODE == kGenAtOnce ? 64 : 0;
+    if (tid >= kLook)
+        for (int e = tid - kLook; e < N * N; e += 256 - kLook) lft[(e % N) * N + e / N] = LF[e];
+    if (tid < rows) {
+        const int64_t k = segment_of(seg_off, n_pts, r0 + tid);
+        const int64_t pk = p[k];
+        pk_s[tid] = (pk >= 0 && pk < G) ? pk : -1;
+        j_s[tid] = (u_first ? u_first[k] : 0) + (r0 + tid - seg_off[k]);
+        if (p_idx) p_idx[r0 + tid] = pk_s[tid];
     }
+    if (tid == 0) n_slow = 0;
     __syncthreads();
-    // the list pays where there are more draws than threads; else all draws are
-    // left open.  A tile of one point takes the squeeze's constants from a table,
-    // in one of several (short segments) each draw forms its own.
-    const bool squeeze = rows * N > 256, one = squeeze && one_s;  // uniform
-    if (one) {
-        const int64_t p_cs = pk_s[0];
+    const int64_t p_cs = MODE == kGenTable ? pk_s[0] : -2;  // the tabulated point
+    if constexpr (MODE == kGenTable) {
         if (tid < N && p_cs >= 0) {
             lam_s[tid] = S64[p_cs * N + tid];
             cs[tid] = ptrs_constants(lam_s[tid]);
@@ -261,28 +259,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         int64_t n = -1;
         if (pk >= 0) {
             g = normal_draw(seed, pk, j, i);
-            if (squeeze) {
-                const double lam = one ? lam_s[i] : S64[pk * N + i];
+            bool open = true;
+            if (MODE == kGenOwn || (MODE == kGenTable && pk == p_cs)) {
+                const double lam = MODE == kGenTable ? lam_s[i] : S64[pk * N + i];
                 if (lam >= 10.0 && !__builtin_isinf(lam)) {
-                    const Ptrs c = one ? cs[i] : ptrs_constants(lam);
+                    const Ptrs c = MODE == kGenTable ? cs[i] : ptrs_constants(lam);
                     uint64_t w[4];
                     stream_block(seed, pk, j, i, 0, 0, w);
                     double us, V;
                     const double kf = ptrs_candidate(c, lam, w[0], w[1], us, V);
-                    if (ptrs_squeeze(c, us, V)) n = (int64_t)kf;
+                    if (ptrs_squeeze(c, us, V)) {
+                        n = (int64_t)kf;
+                        open = false;
+                    }
                 }
-                if (n < 0) slow[atomicAdd(&n_slow, 1)] = (uint16_t)(u * kMaxBins + i);
             }
+            if (MODE != kGenAtOnce && open)
+                slow[atomicAdd(&n_slow, 1)] = (uint16_t)(u * kMaxBins + i);
         }
         gs[u][i] = g;
         ns[u][i] = n;
     }
     __syncthreads();
-    for (int e = tid; e < (squeeze ? n_slow : rows * N); e += 256) {
-        const int u = squeeze ? slow[e] / kMaxBins : e / N;
-        const int i = squeeze ? slow[e] % kMaxBins : e % N;
-        if (pk_s[u] >= 0)
+    if constexpr (MODE == kGenAtOnce) {
+        if (tid < rows * N) {
+            const int u = tid / N, i = tid - u * N;
+            if (pk_s[u] >= 0)
+                ns[u][i] = poisson_draw(S64[pk_s[u] * N + i], seed, pk_s[u], j_s[u], i);
+        }
+    } else {
+        for (int e = tid; e < n_slow; e += 256) {
+            const int u = slow[e] / kMaxBins, i = slow[e] % kMaxBins;
             ns[u][i] = poisson_draw(S64[pk_s[u] * N + i], seed, pk_s[u], j_s[u], i);
+        }
     }
     __syncthreads();
     // z_i = sum_{l <= i} L_F[i][l] g_l, increasing l
@@ -292,7 +301,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 #pragma unroll 8
         for (int l = 0; l < N; ++l) z = z + lft[l * N + i] * gs[u][l];  // L_F is 0 past i
         const int64_t pk = pk_s[u], n = ns[u][i];
-        const double lam = pk < 0 ? 0.0 : (one ? lam_s[i] : S64[pk * N + i]);
+        const double lam = pk < 0 ? 0.0 : (pk == p_cs ? lam_s[i] : S64[pk * N + i]);
         d[(r0 + u) * N + i] = (n < 0) ? __builtin_nan("") : (double)n + lam * z;
         if (counts) counts[(r0 + u) * N + i] = (int32_t)n;
     }
@@ -309,18 +318,29 @@ hipError_t launch_gen_universes(const fc_grid *g, int64_t n_pts, const int64_t *
                                 int64_t K, double *d, int64_t *p_idx, int32_t *counts,
                                 hipStream_t st)
 {
-    // few universes: as small tiles as one round of resident blocks takes (4000,
-    // one a point, N = 57: tiles of 5 in 1.04 rounds 41 us, of 6 in 0.87 32 us)
+    // (Times of a call in a stream of calls, N = 57.)  As small tiles as one round of
+    // resident blocks takes (4000 universes, one a point: tiles of 5 in 1.04 rounds
+    // 41 us, of 6 in 0.87 32 us); few universes a tile a CU, of at most four rows
+    // (tiles of 1 / 2 / 4 rows: 1000 of one point 17.9 / 13.0 / 11.1 us, 400 of as
+    // many points 14.3 / 15.8 / 17.3).
     static const int slots =  // queried once (thread-safe)
-        resident_slots(reinterpret_cast<const void *>(&k_gen_universes), 256);
-    const int64_t share = (K + slots - 1) / slots;
-    const int rows = share < kGenRows ? (int)share : kGenRows;
+        resident_slots(reinterpret_cast<const void *>(&k_gen_universes<kGenTable>), 256);
+    const int64_t few = std::min<int64_t>(4, std::max<int64_t>(1, (K + 64) / 256));
+    const int rows = (int)std::min<int64_t>(kGenRows, std::max(few, (K + slots - 1) / slots));
+    // The list pays where there are more draws than threads (1000 of one point,
+    // tiles of four rows: 12.9 us through it, 11.1 at once); the table where
+    // most tiles have one point, judged by the mean segment, as their lengths are
+    // known on the device only (table against own constants: 16 segments of
+    // 10 000 480 / 488 us, 300 of 250 246 / 247, 400 of 100 145 / 141).
+    const auto kernel = rows * g->N <= 256             ? k_gen_universes<kGenAtOnce>
+                        : K / n_pts >= 16 * kGenRows ? k_gen_universes<kGenTable>
+                                                     : k_gen_universes<kGenOwn>;
     const int64_t per_launch = (int64_t(1) << 22) * rows;  // blocks x 256 inside 32 bits
     for (int64_t row0 = 0; row0 < K; row0 += per_launch) {
         const int64_t n = K - row0 < per_launch ? K - row0 : per_launch;
-        hipLaunchKernelGGL(k_gen_universes, dim3((unsigned)((n + rows - 1) / rows)), dim3(256), 0,
-                           st, g->S64, g->LF64, g->N, g->G, n_pts, p, seg_off, u_first, seed, row0,
-                           K, rows, d, p_idx, counts);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((n + rows - 1) / rows)), dim3(256), 0, st,
+                           g->S64, g->LF64, g->N, g->G, n_pts, p, seg_off, u_first, seed, row0, K,
+                           rows, d, p_idx, counts);
     }
     return hipGetLastError();
 }
