@@ -43,7 +43,7 @@ constexpr int64_t kFxCandBytes = int64_t(64) << 20;
 // 450 calls (4 to 64 bins, 64 to 10 000 points, groups of 8 to 1000, with and
 // without iteration): the best of eight pairs; (1, 1), rounds alone, takes 2 %
 // longer on average.
-constexpr ChunkRule kFxChunks{1, 32, 3.0, 0.8};
+constexpr ChunkRule kFxChunks{1, 32, 3.0, 3.0, 0.0, 0.8};
 
 struct FxTileDesc {
     int64_t r0;     // first row (group order) of the tile, in the batch

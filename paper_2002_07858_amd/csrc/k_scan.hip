@@ -101,7 +101,7 @@ static hipError_t launch_fp32_n(const fc_grid *g, int64_t K, const double *d, co
     static const int slots =
         resident_slots(reinterpret_cast<const void *>(&k_scan_fp32<N>), 64 * kWavesPerBlock);
     const int64_t tiles = (K + kFp32UnivPerBlock - 1) / kFp32UnivPerBlock;
-    const ScanGeometry sg = scan_geometry(tiles, tiles, nq, slots, nq, kScanChunks);
+    const ScanGeometry sg = scan_geometry(tiles, tiles, nq, slots, nq, kFp32Chunks);
     const int64_t blocks = sg.n_utiles * sg.n_qchunks;
     ProfScope prof(st, "k_scan_fp32");
     hipLaunchKernelGGL((k_scan_fp32<N>), dim3((unsigned)blocks), dim3(64 * kWavesPerBlock), 0, st,

@@ -19,11 +19,16 @@ struct ScanGeometry {
 // With k of the `resident` blocks that fit on a CU, the CU takes max(fill, k)
 // times as long for a unit of all of them as it takes for one block's unit at
 // full rate, and `start` such units for each block's start (staging its
-// universes); fill is the larger of 2.5 blocks and fill_share resident.
+// universes), or `later` for the blocks that follow others on a CU and start
+// while those beside them work; fill is the larger of 2.5 blocks and fill_share
+// resident.  Blocks drift apart, and a launch waits for its last one: `spread` of
+// a CU's last chunks is added.
 struct ChunkRule {
     int64_t least;      // shortest chunk
     int64_t most;       // longest chunk
     double start;
+    double later;
+    double spread;
     double fill_share;
     int64_t soft_chunks = INT64_MAX;  // more chunks than this cost soft_cost units
     double soft_cost = 0.0;
@@ -42,9 +47,17 @@ struct ChunkRule {
 // blocks 70 us; FP32, 100 universes x 10 000 points of 57 bins, 250 blocks of
 // 40 points 117 us, 264 of 38 171 us (eight CUs with two blocks), 500 110 us.
 // More FP64 blocks also mean larger partials, hence no more than fill.  The
-// points scan, with more blocks a CU, fits whole rounds best (0.9 %).
-constexpr ChunkRule kFp64Chunks{4, 2048, 15.0, 0.0}, kScanChunks{4, 2048, 20.0, 0.8},
-    kPointsChunks{4, 2048, 2.0, 1.0};
+// points scan, with more blocks a CU, fits whole rounds best.  Launches of many
+// rounds set the later starts and the spread (72 shapes a form of 12 000 to
+// 204 800 universes, FP64 44 to 100 000; 47 of 1200 to 14 000 grouped by point):
+// without them FP64 / FP32 / points were 2.1 / 2.7 / 4.1 % from the best count
+// on average, with them 0.5 / 0.3 / 0.6 % (FP32, 22 528 universes x 1600 points of
+// 57 bins: 11 chunks 1.25 ms, 23 chunks 1.21 ms; points, 200 x 65 universes x
+// 10 000 points of 20 bins: 8 chunks 2.77 ms, 42 chunks 2.60 ms).  Split BF16 /
+// FP16 are 0.6 / 0.8 % off; with later starts of 2 3.8 / 6.7 %.
+constexpr ChunkRule kFp64Chunks{4, 2048, 15.0, 1.0, 0.06, 0.0},
+    kFp32Chunks{4, 2048, 20.0, 2.0, 0.1, 0.8}, kScanChunks{4, 2048, 20.0, 15.0, 0.03, 0.8},
+    kPointsChunks{4, 2048, 2.0, 2.0, 0.1, 1.0};
 
 // Time of a launch in c chunks, in units of one block's unit at full rate: whole
 // rounds of resident blocks, and a last one that the CUs share out.
@@ -55,10 +68,11 @@ inline double scan_cost(int64_t tiles, int64_t G, int slots, const ChunkRule &ru
     const int64_t resident = slots / cus, blocks = tiles * n;
     const int64_t rounds = blocks / slots, last = (blocks - rounds * slots + cus - 1) / cus;
     const double fill = std::max(2.5, rule.fill_share * (double)resident);
-    const auto time = [&](int64_t k) {
-        return k ? (double)q * std::max(fill, (double)k) + rule.start * (double)k : 0.0;
-    };
-    return (double)rounds * time(resident) + time(last) +
+    const auto work = [&](int64_t k) { return k ? (double)q * std::max(fill, (double)k) : 0.0; };
+    const int64_t first = rounds ? resident : last;  // blocks of a CU that start together
+    const int64_t after = rounds * resident + last - first;
+    return (double)rounds * work(resident) + work(last) + rule.start * (double)first +
+           rule.later * (double)after + rule.spread * work(last ? last : resident) +
            (n > rule.soft_chunks ? rule.soft_cost : 0.0);
 }
 
@@ -66,7 +80,7 @@ inline double scan_cost(int64_t tiles, int64_t G, int slots, const ChunkRule &ru
 // resident blocks, at most max_chunks chunks: the count of the least scan_cost.
 // All blocks of a launch take about the same time, one chunk each, so a round
 // that is not full is lost (FP64, 1000 tiles x 10 000 points on 768 slots: 5
-// chunks in 6.5 rounds 67.6 ms, 13 in 16.9 rounds 64.5 ms; split FP16, 20 tiles
+// chunks in 6.5 rounds 67.6 ms, 23 in 29.95 rounds 65.2 ms; split FP16, 20 tiles
 // x 216 000 points on 512 slots: 106 chunks in 4.1 rounds 12.7 ms, 128 in 5.0
 // rounds 11.0 ms).  The best count is an end of the range or the most chunks
 // that j blocks a CU hold, and what a last round loses matters little once j is
