@@ -102,17 +102,17 @@ FP64_SOURCES = ("paper_2002_07858_amd/csrc/k_scan64.hip",
 # FETCH_SIZE (KiB x 1024 x 2.0000) + WRITE_SIZE (KiB x 1024 x 1.0000) of one launch
 # (a leg's: mean of the three launches of one run)
 TRAFFIC = {
-    ("c5", "fp64", "points"): {"bytes_per_launch": 403635413 * 2048 + 2606250 * 1024,
-                               "source_hash": "c406df0b45783586", "sources": FP64_SOURCES,
+    ("c5", "fp64", "points"): {"bytes_per_launch": 402013070 * 2048 + 2781250 * 1024,
+                               "source_hash": "5afd8f57989492d2", "sources": FP64_SOURCES,
                                "profile": "profiles/c5_all_forms.md"},
-    ("c5", "fp32", "points"): {"bytes_per_launch": 135338415 * 2048 + 641250 * 1024,
-                               "source_hash": "e71eb811567acd9c", "sources": FP32_SOURCES,
+    ("c5", "fp32", "points"): {"bytes_per_launch": 135361951 * 2048 + 641250 * 1024,
+                               "source_hash": "1f8b241aa201b17f", "sources": FP32_SOURCES,
                                "profile": "profiles/c5_all_forms.md"},
-    ("c5", "split_fp16", "points"): {"bytes_per_launch": 2114617807 * 2048 + 2561250 * 1024,
-                                     "source_hash": "fb24f893ecc32653", "sources": SPLIT_SOURCES,
+    ("c5", "split_fp16", "points"): {"bytes_per_launch": 2076164547 * 2048 + 2561250 * 1024,
+                                     "source_hash": "26710d66f17faa25", "sources": SPLIT_SOURCES,
                                      "profile": "profiles/c5_all_forms.md"},
-    ("c5", "split_bf16", "points"): {"bytes_per_launch": 551871122 * 2048 + 6721251 * 1024,
-                                     "source_hash": "fb24f893ecc32653", "sources": SPLIT_SOURCES,
+    ("c5", "split_bf16", "points"): {"bytes_per_launch": 459434559 * 2048 + 6721251 * 1024,
+                                     "source_hash": "26710d66f17faa25", "sources": SPLIT_SOURCES,
                                      "profile": "profiles/c5_all_forms.md"},
 }
 
